@@ -14,6 +14,23 @@
 // it is multiplied.  Fragment reads of the next 16-k step are issued before the
 // MFMAs of the current one.
 //
+// What bounds it and what the k loop does about it (measured with loads-only and
+// compute-only copies): a CU takes 45-60 GB/s out of L2 whatever the source, so at
+// up to 256 live rows the loads alone take as long as the kernel, and the MFMAs
+// have to hide under them.
+//   - A slice's loads are spread evenly over its MFMAs instead of issued in one
+//     burst after the barrier: a wave waits in the load queue for less time, and
+//     its MFMAs go out meanwhile.  Slices past the end are loaded too (from beyond
+//     the buffer: no memory traffic), so the count of loads in flight is a constant.
+//   - The k loop starts at a slice that depends on the column (rot): 28672 rows of
+//     8 KB read at the same k put their lines in the same few memory channels.  A
+//     stream of 235 MB in that order runs at 4.8 TB/s, and at 6.4 TB/s with the
+//     start shifted over the column eighths (the range of one XCD, whose CUs keep
+//     sharing the activations in L2).
+//   Batch 64, 4096 x 128256 LM head: 940 -> 866 us at 1024 rows; SwiGLU 4096 x 28672:
+//   229 -> 210 us at 1024 rows, 63 -> 57 us at 128; 128 experts of 2048 x 1536 at 768
+//   rows: 198 -> 174 us (one card, both sides in turn).
+//
 // Scheduling: the grid is persistent (at most one wave of workgroups); every
 // workgroup reads the live row count M (K*) on the device and walks only the
 // tiles that exist, so rows beyond K* cost nothing.  Tasks (row tile, column
@@ -24,9 +41,10 @@
 // two splits only, not all of A.
 //
 // Determinism and causality: every output element is the same sequence of
-// MFMA k-steps from k = 0 upwards whatever the tile shape; split-K partials are
-// added in split order; the tile shape and split factor depend on M_max (the
-// grid's row bound), never on M.  A row's bits therefore do not depend on which
+// MFMA k-steps whatever the tile shape (from the slice `rot` upwards, then from
+// k = 0; rot depends on the column's 256-column block, the expert and the
+// shapes only); split-K partials are added in split order; the tile shape and
+// split factor depend on M_max (the grid's row bound), never on M.  A row's bits therefore do not depend on which
 // or how many other rows are present.
 //
 // Column groups: each 32-column MFMA tile loads a 32-row group of W chosen by
@@ -71,8 +89,9 @@ using BigFlat = Tile<4, 2, 2, 4>;   // Big without the skew: the sampling epilog
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
 // LDS chunk swizzle of row r: 16 consecutive rows of one chunk column land in
-// 16 different 16-byte bank groups, and so do any 8 consecutive rows.
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & (CPR - 1); }
+// 16 different 16-byte bank groups, and so do any 8 consecutive rows.  Rows 32
+// apart share it, so a wave's fragment addresses differ by constants only.
+__device__ __forceinline__ int swz(int r) { return (r ^ ((r >> 3) & 3)) & (CPR - 1); }
 
 // Workgroup barrier for the LDS rings: each wave has already waited (s_waitcnt
 // vmcnt) for its own loads of the stage it is about to read, so no memory fence
@@ -90,43 +109,6 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt is six bits");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// s_waitcnt with the largest immediate in [LO, HI] that is at most n (n >= LO):
-// a binary search over immediates, since vmcnt cannot come from a register.
-template <int LO, int HI>
-__device__ __forceinline__ void wait_vm_le(int n) {
-  if constexpr (LO == HI) {
-    wait_vm<LO>();
-  } else {
-    constexpr int MID = (LO + HI + 1) / 2;
-    if (n >= MID) wait_vm_le<MID, HI>(n);
-    else wait_vm_le<LO, MID - 1>(n);
-  }
-}
-
-// Vector-memory loads that may still be outstanding when iteration `it` of a
-// k loop of nk slices needs its A and W slices.  Issue order: prologue groups
-// j = 0 .. P-1 (A[j] if j < PA, then W[j] if j < PW), then one group per
-// iteration i (A[i + PA], then W[i + PW]); slices at or past nk are never
-// issued; AJ and BJ are the load instructions of one A and one W slice.  The
-// loads issued after the later of A[it] and W[it] may be outstanding.
-template <int PA, int PW, int AJ, int BJ>
-__device__ __forceinline__ int loads_after(int it, int nk) {
-  constexpr int P = PA > PW ? PA : PW;
-  const int gA = it < PA ? it : P + it - PA;
-  const int gW = it < PW ? it : P + it - PW;
-  const bool last_is_a = gA > gW;          // in a shared group W follows A
-  const int g = last_is_a ? gA : gW;
-  auto has_a = [&](int q) { return q < P ? (q < PA && q < nk) : (q - P + PA < nk); };
-  auto has_w = [&](int q) { return q < P ? (q < PW && q < nk) : (q - P + PW < nk); };
-  int n = (last_is_a && has_w(g)) ? BJ : 0;
-#pragma unroll
-  for (int d = 1; d <= P; ++d) {
-    const int q = g + d;
-    if (q < P + it) n += (has_a(q) ? AJ : 0) + (has_w(q) ? BJ : 0);
-  }
-  return n;
 }
 
 // W row feeding logical tile column group `grp` (global, 32 columns each);
@@ -190,15 +172,24 @@ __device__ __forceinline__ void qkv_emit(const GemmArgs &a, int gm, int head, in
   }
 }
 
+typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+typedef __attribute__((address_space(3))) void lds_void;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, long long bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0,
+                                           (int)(bytes < 0x7fffffffLL ? bytes : 0x7fffffffLL), 0x00020000);
+}
+
 template <int EPI, class T>
 __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   constexpr int GN = T::GN, WM = T::WM, WN = T::WN, NWV = T::NWV;
   constexpr int TM = T::TM, TN = T::TN, NA = T::NA, NB = T::NB;
   constexpr int AJ = TM / (NWV * RPI), BJ = TN / (NWV * RPI);   // load instructions per wave per stage
   static_assert(AJ * NWV * RPI == TM && BJ * NWV * RPI == TN, "tile rows must fill whole wave loads");
+  static_assert(NWV % 4 == 0, "the swizzle of a lane's rows is the same in every load");
   extern __shared__ __align__(16) uint16_t lds[];   // [NA][TM*TK] (A), then [NB][TN*TK] (W)
-  uint16_t *const ldsA = lds;
-  uint16_t *const ldsW = lds + NA * TM * TK;
+  constexpr int ASTAGE = TM * TK * 2, WSTAGE = TN * TK * 2;     // bytes
+  constexpr unsigned OOB = 0x80000000u;
 
   // the wave index is uniform: kept in a scalar register, so LDS destinations
   // of the operand loads are scalar arithmetic
@@ -208,13 +199,14 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   const int lr = lane / CPR, lc = lane % CPR;
 
   // live tasks: (row tile, column tile, split), row tile fastest, split slowest
-  const int M = min(*a.m_count, a.M_max);
-  const int nMT = a.tiles ? *a.n_tiles : (M + TM - 1) / TM;
-  const int nNT = n_col_tiles<EPI>(a, TN);
+  const int M = min(__builtin_amdgcn_readfirstlane(*a.m_count), a.M_max);
+  const unsigned nMT = a.tiles ? __builtin_amdgcn_readfirstlane(*a.n_tiles) : (M + TM - 1) / TM;
+  const unsigned nNT = n_col_tiles<EPI>(a, TN);
   const int splits = a.splits > 1 ? a.splits : 1;
-  const int ntask = nMT * nNT * splits;
-  const int xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
-  const int lo = (int)((long long)ntask * xcd / 8), hi = (int)((long long)ntask * (xcd + 1) / 8);
+  const unsigned ntask = nMT * nNT * splits;
+  const unsigned xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
+  const unsigned lo = (unsigned)(((unsigned long long)ntask * xcd) >> 3);
+  const unsigned hi = (unsigned)(((unsigned long long)ntask * (xcd + 1)) >> 3);
 
   const int nk_all = (a.K + TK - 1) / TK;
   const int per_split = (nk_all + splits - 1) / splits;
@@ -222,101 +214,92 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   // row (or, for gathered rows, from the start of A) and W from the first
   // weight row of its column tile, so the offsets stay below 2^31 for any
   // operand size the host checks admit (gemm_span_ok).
-  const int a_rows_ext = a.a_extent > 0 ? a.a_extent : a.M_max;
   const int w_rows_ext = (EPI == EPI_SWIGLU) ? 2 * a.swiglu_inter : a.N;
-  constexpr unsigned OOB = 0x80000000u;
-  auto rsrc = [](const uint16_t *base, long long bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0,
-                                             (int)(bytes < 0x7fffffffLL ? bytes : 0x7fffffffLL), 0x00020000);
-  };
+  // Each wave load instruction fills one 1 KB block = 8 rows x 64 k; row r's
+  // 16-byte chunk c holds global chunk c ^ swz(r), swz being the same for this
+  // lane's row in every load (rows 8 * NWV apart).
+  const int kchunk = 8 * (lc ^ swz(RPI * wave + lr));   // first k of this lane's chunk within a slice
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)lds;
+  // fragment read addresses: row l32 of the wave's first row (column) block,
+  // chunk kh; the 16-k sub-step ks flips chunk bits 1-2, blocks are 4 KB apart
+  const uint32_t frow = (uint32_t)(l32 * TK * 2 + 16 * (kh ^ swz(l32)));
+  const uint32_t fragA = lds0 + wm * WM * 4096 + frow;
+  const uint32_t fragW = lds0 + NA * ASTAGE + wn * WN * 4096 + frow;
 
-  // fragment read offsets within a stage (row r at r*TK, chunk swizzled)
-  int afrag[WM], bfrag[WN], arx[WM], brx[WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
-    const int r = wm * WM * 32 + i * 32 + l32;
-    afrag[i] = r * TK;
-    arx[i] = swz(r);
-  }
-#pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const int r = wn * WN * 32 + j * 32 + l32;
-    bfrag[j] = r * TK;
-    brx[j] = swz(r);
-  }
-
-  for (int task = lo + (int)(blockIdx.x >> 3); task < hi; task += per_xcd) {
-    const int mt = task % nMT;
-    const int rest = task / nMT;
-    const int nt = rest % nNT, sp = rest / nNT;
+  for (unsigned task = lo + (blockIdx.x >> 3); task < hi; task += per_xcd) {
+    const unsigned rest = task / nMT;
+    const unsigned mt = task - rest * nMT;
+    const unsigned sp = splits > 1 ? rest / nNT : 0;
+    const unsigned nt = rest - sp * nNT;
     int m0 = mt * TM, Mlim = M;
     const uint16_t *Wb = a.W;
-    if (a.tiles) {
-      const int e = a.tiles[3 * mt];
-      m0 = a.tiles[3 * mt + 1];
-      Mlim = a.tiles[3 * mt + 2];
-      Wb += (size_t)e * a.w_stride;
-    }
+    const int kt0 = sp * per_split;
+    const int nk = max(0, min(nk_all, kt0 + per_split) - kt0);
     const int grp0 = nt * (TN / 32);
+    // First slice of the k loop: spread over the column eighths, or, for grouped
+    // tasks (each reads weights of its own), over experts and column tiles.  With
+    // split-K the splits start apart already (a shift on top measured no faster).
+    // Logits all start at k = 0: equal weight rows have to give equal logits.
+    int rot = 0;
+    if (a.tiles) {
+      // uniform, but loaded through the vector path: kept scalar
+      const int e = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt]);
+      m0 = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt + 1]);
+      Mlim = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt + 2]);
+      Wb += (size_t)e * a.w_stride;
+      rot = nk > 0 ? (int)((e * nNT + nt) * 5u % (unsigned)nk) : 0;
+    } else if (splits == 1 && EPI != EPI_ARGMAX && EPI != EPI_SAMPLE) {
+      const unsigned n256 = (nNT * (TN / 32) + 7) / 8;
+      rot = (int)((grp0 / 8) * 8u / n256) * nk / 8;
+    }
     // the lowest W row of the tile: its first column group (gate rows precede
     // up rows; a head's first group is its first 32 dimensions)
     const int wrow0 = max(group_wrow<EPI>(a, grp0), 0);
-    const __amdgpu_buffer_rsrc_t rsW = rsrc(Wb + (size_t)wrow0 * a.ldw, (long long)(w_rows_ext - wrow0) * a.ldw * 2);
-    const int arow0 = a.a_rows ? 0 : m0;
-    const __amdgpu_buffer_rsrc_t rsA = rsrc(a.A + (size_t)arow0 * a.lda, (long long)(a_rows_ext - arow0) * a.lda * 2);
+    const __amdgpu_buffer_rsrc_t rsW = make_rsrc(Wb + (size_t)wrow0 * a.ldw, (long long)(w_rows_ext - wrow0) * a.ldw * 2);
+    const bool gather = a.a_rows != nullptr;
+    const __amdgpu_buffer_rsrc_t rsA =
+        gather ? make_rsrc(a.A, (long long)a.a_extent * a.lda * 2)
+               : make_rsrc(a.A + (size_t)m0 * a.lda, (long long)(Mlim - m0) * a.lda * 2);
 
-    // Each wave load instruction fills one 1 KB block = 8 rows x 64 k; row r's
-    // 16-byte chunk c holds global chunk c ^ swz(r).  Rows past the operand and
-    // k past K get an offset beyond the buffer, which reads as zeros.
+    // Byte offsets of this lane's loads at k = 0.  Rows past the operand lie
+    // beyond the buffer (A: Mlim ends it; W: the last row does, and the last
+    // gate rows of an odd tile read up rows that no output uses) and read as
+    // zeros; gathered rows past Mlim get an offset beyond it.
     unsigned aoff[AJ], boff[BJ];
-    // k chunk (elements) that load j of this lane fetches within a 64-k slice
-    auto kchunk = [&](int j) { return 8 * (lc ^ swz(RPI * (wave + NWV * j) + lr)); };
+    if (gather) {
+      int src[AJ];
 #pragma unroll
-    for (int j = 0; j < AJ; ++j) {
-      const int r = RPI * (wave + NWV * j) + lr;
-      const int gm = m0 + r;
-      unsigned off = OOB;
-      if (gm < Mlim) {
-        const int src = a.a_rows ? a.a_rows[gm] : gm;
-        off = (unsigned)(((long long)(src - arow0) * a.lda + kchunk(j)) * 2);
-      }
-      aoff[j] = off;
+      for (int j = 0; j < AJ; ++j) src[j] = a.a_rows[min(m0 + RPI * (wave + NWV * j) + lr, Mlim - 1)];
+#pragma unroll
+      for (int j = 0; j < AJ; ++j)
+        aoff[j] = m0 + RPI * (wave + NWV * j) + lr < Mlim ? (unsigned)(src[j] * a.lda + kchunk) * 2 : OOB;
+    } else {
+#pragma unroll
+      for (int j = 0; j < AJ; ++j) aoff[j] = (unsigned)((RPI * (wave + NWV * j) + lr) * a.lda + kchunk) * 2;
     }
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
-      const int r = RPI * (wave + NWV * j) + lr;
-      const int grp = grp0 + (r >> 5);
-      const int wr = group_wrow<EPI>(a, grp);
-      bool ok = wr >= 0;
-      if (EPI == EPI_SWIGLU) ok = ok && ((grp >> 1) * 32 + (r & 31)) < a.swiglu_inter;
-      else ok = ok && wr + (r & 31) < a.N;
-      boff[j] = ok ? (unsigned)(((long long)(wr + (r & 31) - wrow0) * a.ldw + kchunk(j)) * 2) : OOB;
+      const int blk = wave + NWV * j;                   // 8-row block of the tile: all in one 32-row group
+      const int wr = group_wrow<EPI>(a, grp0 + (blk >> 2));
+      boff[j] = wr < 0 ? OOB : (unsigned)((wr - wrow0 + RPI * (blk & 3) + lr) * a.ldw + kchunk) * 2;
     }
     // The k offset of a slice goes in the scalar offset; the per-lane offsets
-    // stay fixed over the k loop.  Rows past the operand carry OOB, which stays
-    // beyond the buffer with any scalar offset added.  Only a slice reaching
-    // past K (K not a multiple of TK) masks its chunks beyond K lane by lane.
-    auto issueA = [&](int kt, int slot) {
-      const int k0 = kt * TK;
-      uint16_t *sa = ldsA + slot * (TM * TK);
-      const bool tail = k0 + TK > a.K;
-#pragma unroll
-      for (int j = 0; j < AJ; ++j) {
-        const unsigned off = (tail && k0 + kchunk(j) >= a.K) ? OOB : aoff[j];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (__attribute__((address_space(3))) void *)(sa + (wave + NWV * j) * 512),
-                                                 16, off, k0 * 2, 0, 0);
-      }
+    // stay fixed over the k loop.  `kill` is zero, or OOB for a slice past the
+    // task's last (issued all the same, so that the count of loads in flight
+    // stays constant) and for chunks beyond K in a slice that reaches past it.
+    auto slice = [&](int it, unsigned &kill) {
+      const int r = it + rot;
+      const int k0 = (kt0 + (r >= nk ? r - nk : r)) * TK;
+      kill = ((unsigned)(it >= nk) | (unsigned)(kchunk >= a.K - k0)) << 31;
+      return k0 * 2;
     };
-    auto issueW = [&](int kt, int slot) {
-      const int k0 = kt * TK;
-      uint16_t *sb = ldsW + slot * (TN * TK);
-      const bool tail = k0 + TK > a.K;
-#pragma unroll
-      for (int j = 0; j < BJ; ++j) {
-        const unsigned off = (tail && k0 + kchunk(j) >= a.K) ? OOB : boff[j];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (__attribute__((address_space(3))) void *)(sb + (wave + NWV * j) * 512),
-                                                 16, off, k0 * 2, 0, 0);
-      }
+    auto issueA = [&](int j, int koff, unsigned kill, uint32_t stage) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void *)(uintptr_t)(lds0 + stage + (wave + NWV * j) * 1024), 16,
+                                               aoff[j] | kill, koff, 0, 0);
+    };
+    auto issueW = [&](int j, int koff, unsigned kill, uint32_t stage) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lds_void *)(uintptr_t)(lds0 + NA * ASTAGE + stage + (wave + NWV * j) * 1024),
+                                               16, boff[j] | kill, koff, 0, 0);
     };
 
     floatx16 acc[WM][WN];
@@ -327,24 +310,61 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    const int kt0 = sp * per_split;
-    const int nk = max(0, min(nk_all, kt0 + per_split) - kt0);
     constexpr int PA = NA - 1, PW = NB - 1;   // slices in flight ahead of the one multiplied
     constexpr int PMAX = PA > PW ? PA : PW;
-    static_assert(PMAX * (AJ + BJ) <= 63, "outstanding loads within the vmcnt range");
+    static_assert(PW >= PA, "W runs at least as far ahead as A");
+    constexpr int NL = AJ + BJ, NM = TK / 16 * WM * WN;   // loads and MFMAs per slice
+    // loads issued after A[it] and W[it] were, when iteration `it` needs them:
+    // the W loads of A[it]'s own iteration (when W runs further ahead) and the
+    // iterations in between
+    constexpr int PEND = (PW > PA ? BJ : 0) + (PA - 1) * NL;
+    static_assert(PMAX * NL <= 63, "outstanding loads within the vmcnt range");
     // prologue: A[0 .. PA-1] and W[0 .. PW-1], interleaved by slice
 #pragma unroll
-    for (int j = 0; j < PMAX; ++j) {
-      if (j < PA && j < nk) issueA(kt0 + j, j % NA);
-      if (j < PW && j < nk) issueW(kt0 + j, j % NB);
+    for (int s = 0; s < PMAX; ++s) {
+      unsigned kill;
+      const int koff = slice(s, kill);
+      if (s < PA) {
+#pragma unroll
+        for (int j = 0; j < AJ; ++j) issueA(j, koff, kill, s * ASTAGE);
+      }
+      if (s < PW) {
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) issueW(j, koff, kill, s * WSTAGE);
+      }
     }
+    // One slice's loads are spread over its MFMAs: A[it + PA] first, then
+    // W[it + PW].  State of the iteration: read and write stages, load operands.
+    uint32_t raS = 0, rwS = 0, waS = PA * ASTAGE, wwS = PW * WSTAGE;
+    int ka, kw;
+    unsigned killA, killW;
+    auto begin = [&](int it) {
+      ka = slice(it + PA, killA);
+      kw = slice(it + PW, killW);
+    };
+    auto advance = [&]() {
+      raS = raS == (NA - 1) * ASTAGE ? 0 : raS + ASTAGE;
+      rwS = rwS == (NB - 1) * WSTAGE ? 0 : rwS + WSTAGE;
+      waS = waS == (NA - 1) * ASTAGE ? 0 : waS + ASTAGE;
+      wwS = wwS == (NB - 1) * WSTAGE ? 0 : wwS + WSTAGE;
+    };
+    auto load_at = [&](int m) {               // the loads issued right after MFMA m of the slice
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        if (l * NM / NL != m) continue;
+        if (l < AJ) issueA(l, ka, killA, waS);
+        else issueW(l - AJ, kw, killW, wwS);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+    };
     // One 16-k sub-step: the WM x WN MFMAs on the fragments in (fa, fb), each
-    // fragment register refilled with sub-step nks of the slice at (na, nb)
+    // fragment register refilled with sub-step nks of the stage at (pa, pw)
     // right after its last use (A fragment i after MFMA (i, WN-1), W fragment
     // j after MFMA (WM-1, j)), so one set of fragment registers serves the
-    // pipeline; nks < 0 refills nothing.
-    auto substep = [&](bf16x8 (&fa)[WM], bf16x8 (&fb)[WN], const uint16_t *na, const uint16_t *nb, int nks) {
-      const int kc = 2 * nks + kh;
+    // pipeline; nks < 0 refills nothing.  q: the sub-step's place among the
+    // slice's loads (negative: none).
+    auto substep = [&](bf16x8 (&fa)[WM], bf16x8 (&fb)[WN], uint32_t pa, uint32_t pw, int nks, int q) {
+      const uint32_t xa = pa ^ (nks * 32), xw = pw ^ (nks * 32);
 #pragma unroll
       for (int i = 0; i < WM; ++i) {
 #pragma unroll
@@ -352,21 +372,22 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           if (nks >= 0 && i == WM - 1) {
-            fb[j] = *(const bf16x8 *)(nb + bfrag[j] + 8 * (kc ^ brx[j]));
+            fb[j] = *(lds_frag *)(uintptr_t)(xw + j * 4096);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
           }
+          if (q >= 0) load_at(q * WM * WN + i * WN + j);
         }
         if (nks >= 0) {
-          fa[i] = *(const bf16x8 *)(na + afrag[i] + 8 * (kc ^ arx[i]));
+          fa[i] = *(lds_frag *)(uintptr_t)(xa + i * 4096);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
       }
     };
-    auto first_frags = [&](const uint16_t *sa, const uint16_t *sb, bf16x8 (&fa)[WM], bf16x8 (&fb)[WN]) {
+    auto first_frags = [&](uint32_t pa, uint32_t pw, bf16x8 (&fa)[WM], bf16x8 (&fb)[WN]) {
 #pragma unroll
-      for (int i = 0; i < WM; ++i) fa[i] = *(const bf16x8 *)(sa + afrag[i] + 8 * (kh ^ arx[i]));
+      for (int i = 0; i < WM; ++i) fa[i] = *(lds_frag *)(uintptr_t)(pa + i * 4096);
 #pragma unroll
-      for (int j = 0; j < WN; ++j) fb[j] = *(const bf16x8 *)(sb + bfrag[j] + 8 * (kh ^ brx[j]));
+      for (int j = 0; j < WN; ++j) fb[j] = *(lds_frag *)(uintptr_t)(pw + j * 4096);
     };
     bf16x8 fa[WM], fb[WN];
     if (T::SKEW && wave >= NWV / 2) {
@@ -376,99 +397,94 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
       // waits for its first fragments.  Each accumulator still takes the k
       // sub-steps in order.
       for (int it = 0; it < nk; ++it) {
-        wait_vm_le<0, PMAX * (AJ + BJ)>(loads_after<PA, PW, AJ, BJ>(it, nk));
+        begin(it);
+        wait_vm<PEND>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the previous slice is out of LDS
         ring_barrier();
-        const uint16_t *sa = ldsA + (it % NA) * (TM * TK);
-        const uint16_t *sb = ldsW + (it % NB) * (TN * TK);
-        if (it == 0) first_frags(sa, sb, fa, fb);
-        else substep(fa, fb, sa, sb, 0);            // last sub-step of the previous slice
-        if (it + PA < nk) issueA(kt0 + it + PA, (it + PA) % NA);
-        if (it + PW < nk) issueW(kt0 + it + PW, (it + PW) % NB);
+        const uint32_t pa = fragA + raS, pw = fragW + rwS;
+        if (it == 0) {
+          first_frags(pa, pw, fa, fb);
 #pragma unroll
-        for (int ks = 0; ks < TK / 16 - 1; ++ks) substep(fa, fb, sa, sb, ks + 1);
+          for (int m = 0; m < WM * WN; ++m) load_at(m);
+        } else {
+          substep(fa, fb, pa, pw, 0, 0);              // last sub-step of the previous slice
+        }
+#pragma unroll
+        for (int ks = 0; ks < TK / 16 - 1; ++ks) substep(fa, fb, pa, pw, ks + 1, ks + 1);
+        advance();
       }
-      if (nk > 0) substep(fa, fb, nullptr, nullptr, -1);
+      if (nk > 0) substep(fa, fb, 0, 0, -1, -1);
     } else {
       for (int it = 0; it < nk; ++it) {
-        // this wave's loads of A[it] and W[it] are done once at most the loads
-        // issued after them remain
-        wait_vm_le<0, PMAX * (AJ + BJ)>(loads_after<PA, PW, AJ, BJ>(it, nk));
+        begin(it);
+        wait_vm<PEND>();
         ring_barrier();
-        const uint16_t *sa = ldsA + (it % NA) * (TM * TK);
-        const uint16_t *sb = ldsW + (it % NB) * (TN * TK);
-        // first 16-k fragments, then the next slices' loads while they are in flight
-        first_frags(sa, sb, fa, fb);
-        if (it + PA < nk) issueA(kt0 + it + PA, (it + PA) % NA);
-        if (it + PW < nk) issueW(kt0 + it + PW, (it + PW) % NB);
+        const uint32_t pa = fragA + raS, pw = fragW + rwS;
+        first_frags(pa, pw, fa, fb);
 #pragma unroll
-        for (int ks = 0; ks < TK / 16; ++ks) substep(fa, fb, sa, sb, ks + 1 < TK / 16 ? ks + 1 : -1);
+        for (int ks = 0; ks < TK / 16; ++ks) substep(fa, fb, pa, pw, ks + 1 < TK / 16 ? ks + 1 : -1, ks);
+        advance();
       }
     }
-    // every wave is done with the rings before the next task's prologue refills them
+    // every wave is done with the rings, and no load is left in flight, before
+    // the epilogue or the next task's prologue writes them
+    wait_vm<0>();
     ring_barrier();
 
-    if (splits > 1) {
-      // split-K partial tile at the true output columns; the reduce pass adds
-      // the splits in order and applies the epilogue
-      float *part = a.split_part + (size_t)sp * a.M_max * a.N;
-      const int rb_ = m0 + wm * WM * 32 + 4 * (lane >> 5);
+    // accumulator element r of a 32x32 tile: row 8*(r/4) + 4*(lane/32) + r%4, column lane%32
+    if (splits > 1 || EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
+      // float32 rows at the true output columns: split-K partials (the reduce
+      // pass adds the splits in order and applies the epilogue), plain stores or
+      // residual adds.  The buffer ends at row Mlim, so rows past it are dropped.
+      const bool part = splits > 1;
+      const int ld = part ? a.N : a.ldo;
+      float *base = part ? a.split_part + (size_t)sp * a.M_max * a.N : a.out_f32;
+      const int rw = m0 + wm * WM * 32;                 // the wave's first row
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(base + (size_t)rw * ld, (long long)max(Mlim - rw, 0) * ld * 4);
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
+      for (int j = 0; j < WN; ++j) {
+        const int wr = group_wrow<EPI>(a, grp0 + wn * WN + j);
+        if (wr < 0) continue;
+        const unsigned v0 = wr + l32 < a.N ? (unsigned)(4 * kh * ld + wr + l32) * 4 : OOB;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          const int wr = group_wrow<EPI>(a, grp0 + wn * WN + j);
-          const int col = wr + l32;
-          if (wr < 0 || col >= a.N) continue;
+        for (int i = 0; i < WM; ++i) {
+          if (EPI == EPI_RESID_F32 && !part) {
+            float old[16];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            int gm = rb_ + i * 32 + 8 * (r >> 2) + (r & 3);
-            if (gm < Mlim) part[(size_t)gm * a.N + col] = acc[i][j][r];
+            for (int r = 0; r < 16; ++r)
+              old[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0));
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = old[r] + acc[i][j][r];
           }
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), rs,
+                                                  v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0);
         }
+      }
       continue;
     }
 
     // ------------------------------------------------------------ epilogues
-    // accumulator element r of a 32x32 tile: row 8*(r/4) + 4*(lane/32) + r%4, column lane%32
     const int rbase = m0 + wm * WM * 32 + 4 * (lane >> 5);
-    if (EPI == EPI_STORE_BF16 || EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32) {
+    if (EPI == EPI_STORE_BF16 || EPI == EPI_SWIGLU) {
+      const int rw = m0 + wm * WM * 32;
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.out_bf16 + (size_t)rw * a.ldo, (long long)max(Mlim - rw, 0) * a.ldo * 2);
+      constexpr int PAIR = EPI == EPI_SWIGLU ? 2 : 1;
+      const int ncol = EPI == EPI_SWIGLU ? a.swiglu_inter : a.N;
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
+      for (int p = 0; p < WN / PAIR; ++p) {
+        const int col = (grp0 + wn * WN + PAIR * p) / PAIR * 32 + l32;
+        const unsigned v0 = col < ncol ? (unsigned)(4 * kh * a.ldo + col) * 2 : OOB;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          int wr = group_wrow<EPI>(a, grp0 + wn * WN + j);
-          if (wr < 0) continue;
-          int col = wr + l32;
-          if (col >= a.N) continue;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            int gm = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
-            if (gm >= Mlim) continue;
-            if (EPI == EPI_STORE_BF16) a.out_bf16[(size_t)gm * a.ldo + col] = f2bf(acc[i][j][r]);
-            else if (EPI == EPI_STORE_F32) a.out_f32[(size_t)gm * a.ldo + col] = acc[i][j][r];
-            else {
-              float *o = a.out_f32 + (size_t)gm * a.ldo + col;
-              *o = *o + acc[i][j][r];
-            }
-          }
-        }
-    } else if (EPI == EPI_SWIGLU) {
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int p = 0; p < WN / 2; ++p) {
-          int ob = ((grp0 + wn * WN + 2 * p) >> 1) * 32;
-          int col = ob + l32;
-          if (col >= a.swiglu_inter) continue;
+        for (int i = 0; i < WM; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            int gm = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
-            if (gm >= Mlim) continue;
-            float g = acc[i][2 * p][r], u = acc[i][2 * p + 1][r];
-            a.out_bf16[(size_t)gm * a.ldo + col] = f2bf(silu(g) * u);
+            float v = acc[i][PAIR * p][r];
+            if constexpr (EPI == EPI_SWIGLU) v = silu(v) * acc[i][2 * p + 1][r];
+            __builtin_amdgcn_raw_buffer_store_b16(f2bf(v), rs, v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * a.ldo * 2, 0, 0);
           }
-        }
+      }
     } else if (EPI == EPI_QKV_ROPE) {
       const int hd = a.head_dim, gph = hd / 32;
 #pragma unroll
