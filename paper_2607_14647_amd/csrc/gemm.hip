@@ -1,11 +1,12 @@
 // bf16 NT GEMM on gfx950 MFMA with fused epilogues: C = A W^T, A [M][K], W [N][K].
 //
-// Two tile shapes share one kernel template (32x32x16 bf16 MFMA, float32
+// Tile shapes of one kernel template (32x32x16 bf16 MFMA, float32
 // accumulators, k-slices of 64):
 //   Big   256 x 256, eight waves in a 4 x 2 grid, each wave 64 x 128;
 //         160 KB of LDS, one workgroup per CU (dense GEMMs with many tiles);
 //   Small 128 x 128, four waves in a 2 x 2 grid, each wave 64 x 64;
-//         80 KB of LDS, two workgroups per CU (grouped MoE GEMMs, split-K).
+//         80 KB of LDS, two workgroups per CU (grouped MoE GEMMs, small shapes);
+//   Deep  128 x 128, eight waves, deeper rings, one workgroup per CU (float32 GEMMs, split-K).
 // Operands stream from memory straight into LDS (buffer loads with the LDS
 // destination, 128-byte rows of 64 k split in XOR-swizzled 16-byte chunks,
 // hardware zeros for rows and k beyond the operands).  A and W have rings of
@@ -83,6 +84,7 @@ struct Tile {
 using Big = Tile<4, 2, 2, 4, 2, 3, true>;
 using Mid = Tile<2, 4, 2, 2, 2, 3, true>;     // 128 x 256, eight waves in a 2 x 4 grid, 128 KB
 using Small = Tile<2, 2, 2, 2>;
+using Deep = Tile<2, 4, 2, 1, 3, 5>;          // 128 x 128, eight waves, three A and five W slices: 128 KB, one per CU
 using MidDeep = Tile<2, 4, 2, 2, 2, 4, true>;   // 128 x 256 with four W slices: the LM head at few live rows
 using BigFlat = Tile<4, 2, 2, 4>;   // Big without the skew: the sampling epilogue needs its registers
 
@@ -485,7 +487,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
             __builtin_amdgcn_raw_buffer_store_b16(f2bf(v), rs, v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * a.ldo * 2, 0, 0);
           }
       }
-    } else if (EPI == EPI_QKV_ROPE) {
+    } else if constexpr (EPI == EPI_QKV_ROPE && WN % 2 == 0) {
       const int hd = a.head_dim, gph = hd / 32;
 #pragma unroll
       for (int i = 0; i < WM; ++i)
@@ -747,65 +749,109 @@ int cu_count() {
   return c;
 }
 
+// float32 GEMMs (QKV before RoPE, O, down, router), split over k or not: the tile
+// whose rounds of the persistent grid take least, at 0.64, 0.9 and 1.15 us per 64-k
+// slice (measured) for 128 x 128, 128 x 256 and 256 x 256 tiles: 32, 48 and 64 KB out
+// of L2 at 50-57 GB/s per CU.  So the large tile takes over where the rounds of the
+// small ones add up.  Batch 64 at 1024 rows: down 4096 x 14336 133 -> 104 us, O
+// 50 -> 41, QKV 63 -> 58, against 128 x 128 tiles in two workgroups per CU.  The deep
+// rings of the 128 x 128 tile cover the HBM latency where a slice brings few bytes: at
+// 16 rows QKV 17.2 -> 14.4 us and O 15.1 -> 13.5 against a two-slice lead; from 128
+// rows on both leads measured the same.  Every element is the same sequence of MFMA
+// k-steps in all of them.
+template <int EPI>
+__device__ __forceinline__ void gemm_by_rows(const GemmArgs &a) {
+  const unsigned M = min(*a.m_count, a.M_max), G = gridDim.x, sp = a.splits > 1 ? a.splits : 1;
+  auto cost = [&](unsigned tm, unsigned tn, unsigned w) {
+    return ((M + tm - 1) / tm * ((a.N + tn - 1) / tn) * sp + G - 1) / G * w;
+  };
+  const unsigned deep = cost(Deep::TM, Deep::TN, 64), mid = cost(Mid::TM, Mid::TN, 90), big = cost(Big::TM, Big::TN, 115);
+  // without split-K the RoPE epilogue needs both halves of a pair in one wave (two column
+  // groups), which the 128 x 128 tile's waves do not have
+  const bool paired = EPI == EPI_QKV_ROPE && sp == 1;
+  if (!paired && deep <= mid && deep <= big) gemm_tasks<EPI, Deep>(a);
+  else if (mid <= big) gemm_tasks<EPI, Mid>(a);
+  else gemm_tasks<EPI, Big>(a);
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(Big::THREADS)
+k_gemm_f32(GemmArgs a) {
+  static_assert(Deep::THREADS == Big::THREADS && Deep::LDS <= Big::LDS, "one launch shape for all tiles");
+  static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for all tiles");
+  gemm_by_rows<EPI>(a);
+}
+
 template <int EPI, class T>
 int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   const int nMT = a.tiles ? a.m_tiles : (a.M_max + T::TM - 1) / T::TM;
   const int nNT = EPI == EPI_SWIGLU ? (a.swiglu_inter + T::TN / 2 - 1) / (T::TN / 2) : (a.N + T::TN - 1) / T::TN;
-  const int splits = a.splits > 1 ? a.splits : 1;
+  if (a.splits > 1) return DCUT_EINVAL;
   if ((EPI == EPI_ARGMAX || EPI == EPI_SAMPLE) && (!a.amax_keys || a.amax_slots < nNT * T::GN))
     return DCUT_EINVAL;
   if (EPI == EPI_SAMPLE && (!a.row_req || !a.row_pos || !(a.inv_temp >= 0.0f))) return DCUT_EINVAL;
-  if (splits > 1 && ((EPI != EPI_RESID_F32 && EPI != EPI_STORE_F32 && EPI != EPI_QKV_ROPE) || a.tiles ||
-                     !a.split_part || a.N % 4 || (EPI != EPI_QKV_ROPE && a.ldo % 4)))
-    return DCUT_EINVAL;
   // persistent grid: one wave of workgroups, a multiple of 8 (one share per XCD)
-  const long long tasks = (long long)nMT * nNT * splits;
+  const long long tasks = (long long)nMT * nNT;
   long long g = (long long)cu_count() * T::PER_CU;
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
   if (g < 8) g = 8;
-  DCUT_TRY(launch(kid, k_gemm<EPI, T>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a));
-  if (splits > 1 && a.defer_reduce) return DCUT_OK;
-  if (splits > 1 && EPI == EPI_QKV_ROPE) {
+  return launch(kid, k_gemm<EPI, T>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
+}
+
+// k_gemm_f32 and, with split-K, the pass that adds the partials (unless the
+// caller does).  One workgroup per CU, fewer when the 128 x 128 tasks are fewer.
+template <int EPI>
+int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
+  const int splits = a.splits > 1 ? a.splits : 1;
+  if (splits > 1 && (!a.split_part || a.N % 4 || (EPI != EPI_QKV_ROPE && a.ldo % 4))) return DCUT_EINVAL;
+  const long long tasks = (long long)((a.M_max + Deep::TM - 1) / Deep::TM) * ((a.N + Deep::TN - 1) / Deep::TN) * splits;
+  long long g = cu_count();
+  if (tasks < g) g = tasks;
+  g = (g + 7) / 8 * 8;
+  DCUT_TRY(launch(kid, k_gemm_f32<EPI>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a));
+  if (splits == 1 || a.defer_reduce) return DCUT_OK;
+  if (EPI == EPI_QKV_ROPE) {
     const int quads = (a.n_q + 2 * a.n_kv) * (a.head_dim / 8);
     return launch(DCUT_KERNEL_NONE, k_qkv_reduce, dim3((quads + 255) / 256, a.M_max), dim3(256), 0, s, a);
   }
-  if (splits > 1)
-    return launch(DCUT_KERNEL_NONE, k_splitk_reduce, dim3((a.N + 1023) / 1024, a.M_max), dim3(256), 0, s,
-                  (const float *)a.split_part, splits, a.M_max, a.N, a.m_count, a.out_f32, a.ldo,
-                  EPI == EPI_RESID_F32 ? 1 : 0);
-  return DCUT_OK;
+  return launch(DCUT_KERNEL_NONE, k_splitk_reduce, dim3((a.N + 1023) / 1024, a.M_max), dim3(256), 0, s,
+                (const float *)a.split_part, splits, a.M_max, a.N, a.m_count, a.out_f32, a.ldo,
+                EPI == EPI_RESID_F32 ? 1 : 0);
 }
 
-// Big tiles for dense GEMMs with at least one Big tile per CU at M_max rows
-// (the SwiGLU and LM-head GEMMs pick Big or a 128-row tile on the device from
-// the live rows); Small
-// tiles for the others, for grouped (MoE row tiles of 128) and for split-K
-// GEMMs.
+// Grouped (MoE) GEMMs run on row tiles of 128 (Small); the float32 GEMMs choose
+// their tile on the device (k_gemm_f32).  The others: Big tiles with at least one
+// Big tile per CU at M_max rows (the SwiGLU and LM-head GEMMs pick Big or a
+// 128-row tile on the device from the live rows), Small tiles below that.
 template <int EPI>
 int launch_epi(int kid, const GemmArgs &a, hipStream_t s) {
-  if (a.tiles || a.splits > 1) return launch_tile<EPI, Small>(kid, a, s);
-  const long long big_tasks = (long long)((a.M_max + Big::TM - 1) / Big::TM) *
-      (EPI == EPI_SWIGLU ? (a.swiglu_inter + Big::TN / 2 - 1) / (Big::TN / 2) : (a.N + Big::TN - 1) / Big::TN);
-  if (big_tasks < cu_count()) return launch_tile<EPI, Small>(kid, a, s);
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX) {
-    // tile shape chosen on the device from the live row count (one workgroup per CU);
-    // the sampling epilogue keeps the 256-row tile (both paths in one kernel would spill)
-    if (EPI == EPI_ARGMAX && (!a.amax_keys || a.amax_slots < (a.N + MidDeep::TN - 1) / MidDeep::TN * MidDeep::GN))
-      return DCUT_EINVAL;
-    const int g = (cu_count() + 7) / 8 * 8;
-    return launch(kid, k_gemm_dual<EPI>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
-  } else if constexpr (EPI == EPI_SAMPLE) {
-    return launch_tile<EPI, BigFlat>(kid, a, s);
+  if (a.tiles) return launch_tile<EPI, Small>(kid, a, s);
+  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE) {
+    return launch_f32<EPI>(kid, a, s);
   } else {
-    return launch_tile<EPI, Big>(kid, a, s);
+    const long long big_tasks = (long long)((a.M_max + Big::TM - 1) / Big::TM) *
+        (EPI == EPI_SWIGLU ? (a.swiglu_inter + Big::TN / 2 - 1) / (Big::TN / 2) : (a.N + Big::TN - 1) / Big::TN);
+    if (big_tasks < cu_count()) return launch_tile<EPI, Small>(kid, a, s);
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX) {
+      // tile shape chosen on the device from the live row count (one workgroup per CU);
+      // the sampling epilogue keeps the 256-row tile (both paths in one kernel would spill)
+      if (EPI == EPI_ARGMAX && (!a.amax_keys || a.amax_slots < (a.N + MidDeep::TN - 1) / MidDeep::TN * MidDeep::GN))
+        return DCUT_EINVAL;
+      const int g = (cu_count() + 7) / 8 * 8;
+      return launch(kid, k_gemm_dual<EPI>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
+    } else if constexpr (EPI == EPI_SAMPLE) {
+      return launch_tile<EPI, BigFlat>(kid, a, s);
+    } else {
+      return launch_tile<EPI, Big>(kid, a, s);
+    }
   }
 }
 
 }  // namespace
 
 int gemm_splits(int M_max, int N, int K) {
-  // Split-K tasks are Small tiles (128 x 128) over a k range, at most PER_CU of them per CU, and a
+  // Split-K tasks are 128 x 128 tiles over a k range (256 x 256 at many live rows), and a
   // split-K GEMM at few live rows runs at the per-CU load rate: its time is that of the busiest
   // CU.  The factor minimises a model of that time summed over a quarter, a half, three quarters
   // and all of M_ref = min(M_max, 1024) live rows (a large batch verifies far fewer than its

@@ -3,11 +3,12 @@
 Tolerances as for the layer parity tests (2e-2 row-relative, bf16 activations)."""
 import dataclasses
 
+import numpy as np
 import pytest
 
 from paper_2607_14647_amd import workload as wl
-from tests.gpu_common import need_gpu
-from tests.test_gpu_layer import _layer_parity
+from tests.gpu_common import need_gpu, workload
+from tests.test_gpu_layer import _gpu_run, _layer_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +32,22 @@ CASES = {
 def test_gemm_edges(name):
     need_gpu()
     _layer_parity(CASES[name], name, 0)
+
+
+# 1024 rows of a layer whose O and down projections split k: 128 x 128 tiles at 64 live rows,
+# 128 x 256 at 320, 256 x 256 at 1024 (chosen on the device from the live rows)
+_TILES = _cfg(103, 64, 320, hidden=4096, n_q=8, n_kv=2, head_dim=128, inter=4096)
+
+
+def test_tile_choice_keeps_bits():
+    """A row's residual is the same bits whichever tile shape its batch's row count selects (the
+    full-size tests hold 256 and 768 rows of every tile's shapes against the oracle)."""
+    need_gpu()
+    st, w, kv = workload(_TILES, 0)
+    runs = [_gpu_run(_TILES, st, w, kv, [K], [1.0])[0] for K in (64, 320, 576, 1024)]
+    full, cf = runs[-1].x.cpu().numpy(), runs[-1].host("cu")
+    for vs in runs[:-1]:
+        x, cu = vs.x.cpu().numpy(), vs.host("cu")
+        for i in range(_TILES.B):
+            n = cu[i + 1] - cu[i]
+            assert np.array_equal(x[cu[i]: cu[i + 1]], full[cf[i]: cf[i] + n]), i
