@@ -21,6 +21,15 @@
 // Partial (o, m, l) per (row, head, chunk) are merged in chunk order by
 // k_attn_combine; a request with a single chunk is finished in place.
 //
+// What bounds it: the cache stream.  A copy without the compute takes 139 us where
+// the kernel takes 145 (batch 64, 0.8 GB), with or without the tile barrier and with
+// a deeper ring, so the inner loop is kept short enough to hide: fragment addresses
+// are one per-lane constant with the k-step or column tile flipped in, tiles whose
+// keys every row sees take no masks, the softmax scale is folded into one fma per
+// score, and weights use the hardware exp2.  Batch 16 at 128 rows 33 -> 28 us, batch
+// 64 at 1024 rows 173 -> 165; groups of 8 heads (up to 128 rows, two row blocks per
+// wave in three workgroups per CU instead of 8 waves in two) 163 -> 152 us at batch 128.
+//
 // Workgroup b takes item b of the longest-first work order (attn_plan.h),
 // which the layer's first norm kernel builds in one extra workgroup; batches
 // too large to plan and grids of one round of slots number the items
@@ -36,6 +45,7 @@ constexpr int KT = 32;     // keys per tile
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
 
 // Barrier of the LDS ring: each wave has waited (s_waitcnt vmcnt) for its own
 // loads of the stage it reads next, so only the hardware barrier is needed; a
@@ -48,24 +58,26 @@ __device__ __forceinline__ void ring_barrier() {
 }
 
 // Transposing LDS reads (ds_read_b64_tr_b16), four columns x two key halves per
-// call.  They are issued from one asm statement that also waits for them
-// (lgkmcnt(0)), so the compiler only ever sees completed results; it cannot
-// model these reads itself without also draining every LDS-DMA stage still in
-// flight (vmcnt(0)).  The ring protocol (vmcnt wait + barrier) orders them
-// after the DMA writes of the stage they read.
-__device__ __forceinline__ void lds_read_tr16_x8(short4v (&r)[8], const uint32_t (&ad)[8]) {
+// call, the second half HALF bytes after the first.  They are issued from one
+// asm statement that also waits for them (lgkmcnt(0)), so the compiler only
+// ever sees completed results; it cannot model these reads itself without also
+// draining every LDS-DMA stage still in flight (vmcnt(0)).  The ring protocol
+// (vmcnt wait + barrier) orders them after the DMA writes of the stage they
+// read.
+template <int HALF>
+__device__ __forceinline__ void lds_read_tr16_x8(short4v (&r)[8], uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
   asm volatile(
       "ds_read_b64_tr_b16 %0, %8\n\t"
-      "ds_read_b64_tr_b16 %1, %9\n\t"
-      "ds_read_b64_tr_b16 %2, %10\n\t"
-      "ds_read_b64_tr_b16 %3, %11\n\t"
-      "ds_read_b64_tr_b16 %4, %12\n\t"
-      "ds_read_b64_tr_b16 %5, %13\n\t"
-      "ds_read_b64_tr_b16 %6, %14\n\t"
-      "ds_read_b64_tr_b16 %7, %15\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\t"
+      "ds_read_b64_tr_b16 %3, %9 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\t"
+      "ds_read_b64_tr_b16 %5, %10 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\t"
+      "ds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "v"(ad[4]), "v"(ad[5]), "v"(ad[6]), "v"(ad[7])
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "n"(HALF)
       : "memory");
 }
 
@@ -79,8 +91,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void *base,
 
 // NSTAGE LDS ring stages: NSTAGE - 1 tiles in flight while one is used.  At
 // most 168 registers (three waves per SIMD), so three 4-wave workgroups with
-// 3-stage rings (48 KB of LDS each) share a CU.
-template <int HD, int NW, int NSTAGE>
+// 3-stage rings (48 KB of LDS each) share a CU.  A wave owns RB blocks of 16
+// query rows, 16 * NW rows apart; blocks past an item's rows are skipped.
+template <int HD, int NW, int NSTAGE, int RB>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3)))
 k_attn(AttnArgs a) {
   constexpr int ROWB = HD * 2;              // bytes per key row
@@ -96,15 +109,17 @@ k_attn(AttnArgs a) {
 
   const int MC = a.max_chunks;
   const int tid = threadIdx.x, lane = tid & 63;
-  int i, g, c, t0, d, L, cap;
+  int g, c, t0, d, L, cap;
+  int64_t base;                       // first element of the request's slab
   if (a.plan) {
     const int idx = blockIdx.x;
     const int n = a.plan[0];
     const int4 *it = (const int4 *)((const char *)a.plan + PLAN_HEAD) + 2 * idx;
     const int4 e0 = it[0], e1 = it[1];
     if (idx >= n) return;
-    i = e0.x; g = e0.y; c = e0.z; t0 = e0.w;
+    g = e0.y; c = e0.z; t0 = e0.w;
     d = e1.x; L = e1.y; cap = e1.z;
+    base = (int64_t)(((uint64_t)(uint32_t)e1.w << 32) | (uint32_t)e0.x);
   } else {
     // Chunk index slowest: the work items that exist for every request (the
     // first chunks) come first, so workgroups of chunks a request does not
@@ -112,7 +127,7 @@ k_attn(AttnArgs a) {
     const int idx = blockIdx.x;
     c = idx / (a.B * a.n_kv);
     g = idx % a.n_kv;
-    i = (idx / a.n_kv) % a.B;
+    const int i = (idx / a.n_kv) % a.B;
     if (c >= MC) return;
     t0 = a.cu[i];
     d = a.cu[i + 1] - t0;
@@ -124,6 +139,7 @@ k_attn(AttnArgs a) {
     }
     L = usable_ctx(L0, cap, a.D);
     if (c >= n_chunks(L, a.chunk, MC)) return;
+    base = a.kv_base[i];
   }
   const int nc = n_chunks(L, a.chunk, MC);
   const int kstart = c * a.chunk;
@@ -135,38 +151,48 @@ k_attn(AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, grp4 = lane >> 4;
 
-  // this lane's query row
-  const int rr = wave * 16 + l16;
-  const bool row_ok = rr < R;
-  const int hl = row_ok ? rr / d : 0;
-  const int krow = row_ok ? rr - hl * d : 0;
-  const int head = g * G + hl;
-  const int t = t0 + krow;
-  const int kmax = L + krow;          // last visible key position
-  const bool wave_active = wave * 16 < R;
+  // this lane's query rows, one per block
+  bool row_ok[RB];
+  int trow[RB], head[RB], kmax[RB];   // packed row, query head, last visible key position
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int rr = (rb * NW + wave) * 16 + l16;
+    row_ok[rb] = rr < R;
+    const int hl = row_ok[rb] ? rr / d : 0;
+    const int krow = row_ok[rb] ? rr - hl * d : 0;
+    head[rb] = g * G + hl;
+    trow[rb] = t0 + krow;
+    kmax[rb] = L + krow;
+  }
 
-  bf16x8 qf[NS];
-  {
-    const uint16_t *qp = a.q + ((size_t)t * a.n_q + head) * HD + 8 * grp4;
+  bf16x8 qf[RB][NS];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const uint16_t *qp = a.q + ((size_t)trow[rb] * a.n_q + head[rb]) * HD + 8 * grp4;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if (row_ok) qf[s] = *(const bf16x8 *)(qp + 32 * s);
+      if (row_ok[rb]) qf[rb][s] = *(const bf16x8 *)(qp + 32 * s);
       else {
         uint4 z = make_uint4(0, 0, 0, 0);
-        qf[s] = *(bf16x8 *)&z;
+        qf[rb][s] = *(bf16x8 *)&z;
       }
     }
   }
 
-  floatx4 o[NT];
+  floatx4 o[RB][NT];
+  float m_run[RB], l_run[RB];
 #pragma unroll
-  for (int n = 0; n < NT; ++n) o[n] = {0.f, 0.f, 0.f, 0.f};
-  float m_run = -__builtin_inff();
-  float l_run = 0.0f;
-  const float sl2 = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
+  for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) o[rb][n] = {0.f, 0.f, 0.f, 0.f};
+    m_run[rb] = -__builtin_inff();
+    l_run[rb] = 0.0f;
+  }
+  constexpr float sl2 = 1.4426950408889634f / (HD == 128 ? 11.313708498984761f : 8.0f);   // log2(e) / sqrt(hd)
+  static_assert(HD == 64 || HD == 128, "sqrt of the head dimension");
 
-  // K and V of (request i, kv head g) as buffers: out-of-range keys read as zeros
-  const size_t slab = (size_t)a.kv_base[i] + (size_t)g * cap * HD;
+  // K and V of the request's kv head g as buffers: out-of-range keys read as zeros
+  const size_t slab = (size_t)base + (size_t)g * cap * HD;
   const int slab_bytes = cap * ROWB;
   const __amdgpu_buffer_rsrc_t rK = uniform_rsrc(a.kv_k + slab, slab_bytes);
   const __amdgpu_buffer_rsrc_t rV = uniform_rsrc(a.kv_v + slab, slab_bytes);
@@ -192,6 +218,16 @@ k_attn(AttnArgs a) {
     }
   };
 
+  // Fragment addresses within a tile.  K: key row l16 (16-key blocks 16 rows
+  // apart), chunk grp4 ^ (row % CPR), k-step s flips chunk bits 2-3.  V: source
+  // lane s of a 16-lane group reads key row k0 + s/4, columns 16n + 4(s%4)..+3,
+  // and lane d receives keys k0..k0+3 of column 16n + d; the column tile n flips
+  // chunk bits 1-3, the second 16 keys lie 16 rows on.
+  const int vrow = 4 * grp4 + (l16 >> 2);
+  const uint32_t ring0 = (uint32_t)(uintptr_t)(lds_void *)ring;
+  const uint32_t kfrag = ring0 + l16 * ROWB + 16 * (grp4 ^ (l16 % CPR));
+  const uint32_t vfrag = ring0 + TILEB + vrow * ROWB + 16 * (((l16 & 3) >> 1) ^ (vrow % CPR)) + 8 * (l16 & 1);
+
   const int ntiles = (kend - kstart + KT - 1) / KT;
 #pragma unroll
   for (int s = 0; s < NSTAGE - 1; ++s)
@@ -206,116 +242,103 @@ k_attn(AttnArgs a) {
     else __builtin_amdgcn_s_waitcnt(W0);
     ring_barrier();
     if (tile + NSTAGE - 1 < ntiles) issue(tile + NSTAGE - 1, (tile + NSTAGE - 1) % NSTAGE);
-    if (!wave_active) continue;
     const int p0 = kstart + tile * KT;
-    const unsigned char *Ks = ring + (tile % NSTAGE) * STAGEB;
-    const unsigned char *Vs = Ks + TILEB;
+    const uint32_t ks = kfrag + (tile % NSTAGE) * STAGEB, vs = vfrag + (tile % NSTAGE) * STAGEB;
+    // every key of the tile is visible to every row (block key 0 is the bonus token
+    // itself): no masks.  Depends on L and the chunk only, like all of a row's steps.
+    const bool full = p0 + KT <= min(kend, L + 1);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      if ((rb * NW + wave) * 16 >= R) break;   // uniform: no rows in this block or any later one
+      // S^T: two blocks of 16 keys; lane owns keys 4 grp4 + j of each
+      floatx4 s4[KT / 16];
+#pragma unroll
+      for (int kb = 0; kb < KT / 16; ++kb) {
+        s4[kb] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const bf16x8 kf = *(lds_frag *)(uintptr_t)((ks ^ (64 * s)) + kb * 16 * ROWB);
+          s4[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[rb][s], s4[kb], 0, 0, 0);
+        }
+      }
+      if (!full) {
+#pragma unroll
+        for (int kb = 0; kb < KT / 16; ++kb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int p = p0 + kb * 16 + 4 * grp4 + j;
+            if (p >= kend || p > kmax[rb]) s4[kb][j] = -__builtin_inff();
+          }
+      }
+      // tile maximum of the row in the exp2 domain (scores times sl2 > 0)
+      float tmax = fmaxf(fmaxf(s4[0][0], s4[0][1]), fmaxf(s4[0][2], s4[0][3]));
+      tmax = fmaxf(tmax, fmaxf(fmaxf(s4[1][0], s4[1][1]), fmaxf(s4[1][2], s4[1][3])));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64)) * sl2;
+      const float m_new = fmaxf(m_run[rb], tmax);
+      // a row that has seen no key yet keeps m = -inf; subtracting 0 then keeps its weights at 0
+      const float sub = m_new == -__builtin_inff() ? 0.0f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run[rb] - sub);
+      float psum = 0.0f;
+#pragma unroll
+      for (int kb = 0; kb < KT / 16; ++kb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s4[kb][j], sl2, -sub));
+          s4[kb][j] = pv;
+          psum += pv;
+        }
+      psum += __shfl_xor(psum, 16, 64);
+      psum += __shfl_xor(psum, 32, 64);
+      l_run[rb] = l_run[rb] * alpha + psum;
+      m_run[rb] = m_new;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) o[rb][n] *= alpha;
 
-    // S^T: KT/16 blocks of 16 keys; lane reads key row kb*16 + l16, global chunk 4s + grp4
-    floatx4 s4[KT / 16];
-#pragma unroll
-    for (int kb = 0; kb < KT / 16; ++kb) {
-      s4[kb] = {0.f, 0.f, 0.f, 0.f};
-      const int r = kb * 16 + l16;
-      const unsigned char *kp = Ks + r * ROWB;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        bf16x8 kf = *(const bf16x8 *)(kp + 16 * ((4 * s + grp4) ^ (r % CPR)));
-        s4[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[s], s4[kb], 0, 0, 0);
-      }
-    }
-    // mask + scale, tile max
-    float tmax = -__builtin_inff();
-#pragma unroll
-    for (int kb = 0; kb < KT / 16; ++kb)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        int p = p0 + kb * 16 + 4 * grp4 + j;
-        bool vis = row_ok && p < kend && p <= kmax;
-        float v = vis ? s4[kb][j] * sl2 : -__builtin_inff();
-        s4[kb][j] = v;
-        tmax = fmaxf(tmax, v);
-      }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    const float m_new = fmaxf(m_run, tmax);
-    float alpha = 1.0f;
-    if (m_new != -__builtin_inff()) alpha = exp2f(m_run - m_new);
-    float psum = 0.0f;
-#pragma unroll
-    for (int kb = 0; kb < KT / 16; ++kb)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float v = s4[kb][j];
-        float pv = (v == -__builtin_inff()) ? 0.0f : exp2f(v - m_new);
-        s4[kb][j] = pv;
-        psum += pv;
-      }
-    psum += __shfl_xor(psum, 16, 64);
-    psum += __shfl_xor(psum, 32, 64);
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-#pragma unroll
-    for (int n = 0; n < NT; ++n) o[n] *= alpha;
-
-    // O^T += V^T P^T per 32-key step.  P^T slots of this lane: keys 4*grp4+j of the
-    // two 16-key blocks; the V^T fragment with the same keys comes from two
-    // transposing reads: source lane s of a 16-lane group reads key row
-    // k0 + s/4, columns 16n + 4(s%4)..+3, and lane d receives keys k0..k0+3 of
-    // column 16n + d.
-#pragma unroll
-    for (int ks = 0; ks < KT / 32; ++ks) {
+      // O^T += V^T P^T.  P^T slots of this lane: keys 4*grp4+j of the two 16-key
+      // blocks; the V^T fragment with the same keys comes from two transposing reads.
       bf16x8 pf;
       uint32_t *pw = (uint32_t *)&pf;
-      pw[0] = pack_bf2(s4[2 * ks][0], s4[2 * ks][1]);
-      pw[1] = pack_bf2(s4[2 * ks][2], s4[2 * ks][3]);
-      pw[2] = pack_bf2(s4[2 * ks + 1][0], s4[2 * ks + 1][1]);
-      pw[3] = pack_bf2(s4[2 * ks + 1][2], s4[2 * ks + 1][3]);
-      const int r0 = 32 * ks + 4 * grp4 + (l16 >> 2);      // source key row, first half
-      const int r1 = r0 + 16;
-      const int csub = 4 * (l16 & 3);                       // element offset within 16 columns
-      static_assert(NT % 4 == 0, "transposing reads come in groups of four columns");
+      pw[0] = pack_bf2(s4[0][0], s4[0][1]);
+      pw[1] = pack_bf2(s4[0][2], s4[0][3]);
+      pw[2] = pack_bf2(s4[1][0], s4[1][1]);
+      pw[3] = pack_bf2(s4[1][2], s4[1][3]);
+      static_assert(NT % 4 == 0 && KT == 32, "transposing reads come in groups of four columns, one 32-key step");
 #pragma unroll
       for (int n0 = 0; n0 < NT; n0 += 4) {
-        uint32_t ad[8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int col = 16 * (n0 + u) + csub;              // first of 4 columns read
-          const int gc = col >> 3, half = (col & 7) * 2;     // 16-byte chunk, byte offset in it
-          ad[2 * u] = (uint32_t)(uintptr_t)(Vs + r0 * ROWB + 16 * (gc ^ (r0 % CPR)) + half);
-          ad[2 * u + 1] = (uint32_t)(uintptr_t)(Vs + r1 * ROWB + 16 * (gc ^ (r1 % CPR)) + half);
-        }
         short4v vr[8];
-        lds_read_tr16_x8(vr, ad);
+        lds_read_tr16_x8<16 * ROWB>(vr, vs ^ (32 * n0), vs ^ (32 * (n0 + 1)), vs ^ (32 * (n0 + 2)), vs ^ (32 * (n0 + 3)));
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           bf16x8 vf;
           short4v *vw = (short4v *)&vf;
           vw[0] = vr[2 * u];
           vw[1] = vr[2 * u + 1];
-          o[n0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf, o[n0 + u], 0, 0, 0);
+          o[rb][n0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf, o[rb][n0 + u], 0, 0, 0);
         }
       }
     }
   }
-  if (!row_ok) return;
-
   // lane holds O^T[16n + 4*grp4 + j][row]
-  if (nc == 1) {
-    const float inv = l_run > 0.0f ? 1.0f / l_run : 0.0f;
-    uint16_t *op = a.out + ((size_t)t * a.n_q + head) * HD;
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+  for (int rb = 0; rb < RB; ++rb) {
+    if (!row_ok[rb]) continue;
+    if (nc == 1) {
+      const float inv = l_run[rb] > 0.0f ? 1.0f / l_run[rb] : 0.0f;
+      uint16_t *op = a.out + ((size_t)trow[rb] * a.n_q + head[rb]) * HD;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) op[16 * n + 4 * grp4 + j] = f2bf(o[n][j] * inv);
-  } else {
-    float *pp = a.part + (((size_t)t * a.n_q + head) * MC + c) * (HD + 2);
+      for (int n = 0; n < NT; ++n)
+        *(uint2 *)(op + 16 * n + 4 * grp4) = make_uint2(pack_bf2(o[rb][n][0] * inv, o[rb][n][1] * inv),
+                                                        pack_bf2(o[rb][n][2] * inv, o[rb][n][3] * inv));
+    } else {
+      float *pp = a.part + (((size_t)trow[rb] * a.n_q + head[rb]) * MC + c) * (HD + 2);
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
-      *(float4 *)(pp + 16 * n + 4 * grp4) = make_float4(o[n][0], o[n][1], o[n][2], o[n][3]);
-    if (grp4 == 0) {
-      pp[HD] = m_run;
-      pp[HD + 1] = l_run;
+      for (int n = 0; n < NT; ++n)
+        *(float4 *)(pp + 16 * n + 4 * grp4) = make_float4(o[rb][n][0], o[rb][n][1], o[rb][n][2], o[rb][n][3]);
+      if (grp4 == 0) {
+        pp[HD] = m_run[rb];
+        pp[HD + 1] = l_run[rb];
+      }
     }
   }
 }
@@ -415,18 +438,17 @@ k_attn_combine(AttnArgs a, const int32_t *__restrict__ packed_req, int rows_max)
 
 template <int HD>
 int launch_hd(const AttnArgs &a, int rows_max, const int32_t *packed_req, int waves, hipStream_t s) {
-  // Up to 64 rows per item: 4 waves and a 3-stage ring, three workgroups per
-  // CU, so one streams on while another starts or finishes an item.  Up to 128
-  // or 256 rows: 8 or 16 waves and a 4-stage ring, two or one per CU (8 waves
-  // measured faster than 4 at two workgroups per CU: the extra waves share
-  // the tile loads).
+  // Up to 128 rows per item: 4 waves and a 3-stage ring, three workgroups per
+  // CU, so one streams on while another starts or finishes an item; above 64
+  // rows a wave owns two row blocks.  Up to 256 rows: 16 waves and a 4-stage
+  // ring, one workgroup per CU.
   const dim3 grid(a.B * a.n_kv * a.max_chunks);
   if (waves <= 4) {
-    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 4, 3>, grid, dim3(256), 0, s, a));
+    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 4, 3, 1>, grid, dim3(256), 0, s, a));
   } else if (waves <= 8) {
-    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 8, 4>, grid, dim3(512), 0, s, a));
+    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 4, 3, 2>, grid, dim3(256), 0, s, a));
   } else {
-    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 16, 4>, grid, dim3(1024), 0, s, a));
+    DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 16, 4, 1>, grid, dim3(1024), 0, s, a));
   }
   int nw = rows_max * a.n_q;
   return launch(DCUT_KERNEL_ATTN_COMBINE, k_attn_combine<HD>, dim3((nw + 3) / 4), dim3(256), 0, s, a,

@@ -19,8 +19,8 @@
 // order: every item writes its own partial, merged in chunk order.
 //
 // Plan layout: int32 count at offset 0, items from byte PLAN_HEAD on, 8 int32
-// each: {request, kv head, chunk, first packed row, kept rows, usable context,
-// cap, 0}.
+// each: {slab base (low half), kv head, chunk, first packed row, kept rows, usable
+// context, cap, slab base (high half)}: all an item needs in one load.
 #pragma once
 #include "dcut_internal.h"
 
@@ -62,17 +62,20 @@ __device__ __forceinline__ void attn_plan_block(const AttnArgs &a, int *s) {
   int *s_ck = s, *s_w = s_ck + B4;
   const int t = threadIdx.x, w = t >> 6, ln = t & 63;
   int ck[RMAX], full[RMAX], t0s[RMAX], ds[RMAX], Ls[RMAX], caps[RMAX], lasts[RMAX];
+  int64_t bases[RMAX];
   int sum = 0, nl = 0, nv = 0;
 #pragma unroll
   for (int r = 0; r < RMAX; ++r) {
     const int j = t * R + r;
     int key = -1;
     full[r] = t0s[r] = ds[r] = Ls[r] = caps[r] = lasts[r] = 0;
+    bases[r] = 0;
     if (r < R && j < B) {
       const int t0 = a.cu[j];
       const int d = a.cu[j + 1] - t0;
       const int L0 = a.ctx_len[j];
       const int cap = a.kv_cap[j];
+      bases[r] = a.kv_base[j];
       if (d > 0 && (L0 < 0 || L0 + a.D + 1 > cap) && a.dev_err) atomicOr(a.dev_err, DCUT_DERR_CAPACITY);
       const int L = usable_ctx(L0, cap, a.D);
       const int nc = n_chunks(L, CH, MC);
@@ -135,17 +138,18 @@ __device__ __forceinline__ void attn_plan_block(const AttnArgs &a, int *s) {
       const int4 v = k4[k];
       rank += (v.x > ck[r]) + (v.y > ck[r]) + (v.z > ck[r]) + (v.w > ck[r]);
     }
-    const int4 tail = make_int4(ds[r], Ls[r], caps[r], 0);
+    const int b0 = (int)(uint32_t)(uint64_t)bases[r];
+    const int4 tail = make_int4(ds[r], Ls[r], caps[r], (int)(uint32_t)((uint64_t)bases[r] >> 32));
     for (int c = 0; c < full[r]; ++c)
       for (int g = 0; g < nkv; ++g) {
         const int p = pre + c * nkv + g;
-        items[2 * p] = make_int4(j, g, c, t0s[r]);
+        items[2 * p] = make_int4(b0, g, c, t0s[r]);
         items[2 * p + 1] = tail;
       }
     // last chunks: the n_long longer than a chunk first, the others after the full chunks
     const int base = rank < n_long ? rank * nkv : e2 + (rank - n_long) * nkv;
     for (int g = 0; g < nkv; ++g) {
-      items[2 * (base + g)] = make_int4(j, g, lasts[r], t0s[r]);
+      items[2 * (base + g)] = make_int4(b0, g, lasts[r], t0s[r]);
       items[2 * (base + g) + 1] = tail;
     }
   }
