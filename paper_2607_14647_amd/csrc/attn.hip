@@ -331,7 +331,7 @@ k_attn(AttnArgs a) {
         *(uint2 *)(op + 16 * n + 4 * grp4) = make_uint2(pack_bf2(o[rb][n][0] * inv, o[rb][n][1] * inv),
                                                         pack_bf2(o[rb][n][2] * inv, o[rb][n][3] * inv));
     } else {
-      float *pp = a.part + (((size_t)trow[rb] * a.n_q + head[rb]) * MC + c) * (HD + 2);
+      float *pp = a.part + (((size_t)trow[rb] * a.n_q + head[rb]) * MC + c) * ATTN_PITCH(HD);
 #pragma unroll
       for (int n = 0; n < NT; ++n)
         *(float4 *)(pp + 16 * n + 4 * grp4) = make_float4(o[rb][n][0], o[rb][n][1], o[rb][n][2], o[rb][n][3]);
@@ -343,97 +343,72 @@ k_attn(AttnArgs a) {
   }
 }
 
-// One wave per (row, head): merge the chunk partials in chunk order.
+// Merge of a (row, head)'s chunk partials, one half wave each: lane c reads chunk
+// c's (max, sum), so the weights of up to 32 chunks cost one memory round trip,
+// taken together with the first eight chunks' values.  Values add up in chunk
+// order.  Latency-bound (three dependent loads: row and count, context, partials),
+// so a wave carries two pairs and reads its row's index beside the live row count.
 template <int HD>
 __global__ void __launch_bounds__(256)
 k_attn_combine(AttnArgs a, const int32_t *__restrict__ packed_req, int rows_max) {
-  const int wid = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  constexpr int PER = HD / 32, CG = 8;
+  const int lane = threadIdx.x & 31;
+  const int pair = blockIdx.x * 8 + (threadIdx.x >> 5);
+  const int t = pair / a.n_q, head = pair - t * a.n_q;
+  const int req0 = packed_req[min(t, rows_max - 1)];
   const int M = a.cu[a.B];
-  const int t = wid / a.n_q, head = wid - t * a.n_q;
   if (t >= M || t >= rows_max) return;
-  const int req = packed_req[t];
-  if (req < 0 || req >= a.B) return;
+  if (req0 < 0 || req0 >= a.B) return;
   const int MC = a.max_chunks;
-  const int L = usable_ctx(a.ctx_len[req], a.kv_cap[req], a.D);
+  const int L = usable_ctx(a.ctx_len[req0], a.kv_cap[req0], a.D);
   const int nc = n_chunks(L, a.chunk, MC);
   if (nc == 1) return;
-  const float *pp = a.part + ((size_t)t * a.n_q + head) * MC * (HD + 2);
-  // the loads of up to CG chunks are issued together (one memory latency per
-  // group rather than per chunk); the sums still run in chunk order
-  constexpr int CG = 8;
-  constexpr int PER = HD / 64;
-  const float *pl = pp + lane * PER;
-  uint16_t *op = a.out + ((size_t)t * a.n_q + head) * HD;
-  if (nc <= CG) {
-    // every chunk's (max, sum, partial) in one memory round trip; the same
-    // operations in the same order as the two-pass loop below
-    float mv[CG], lv[CG], xv[CG][PER];
-#pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      mv[c] = c < nc ? pp[c * (HD + 2) + HD] : -__builtin_inff();
-      lv[c] = c < nc ? pp[c * (HD + 2) + HD + 1] : 0.0f;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) xv[c][e] = c < nc ? pl[c * (HD + 2) + e] : 0.0f;
-    }
-    float mx = -__builtin_inff();
-#pragma unroll
-    for (int c = 0; c < CG; ++c) mx = fmaxf(mx, mv[c]);
-    float acc[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = 0.0f;
-    float lsum = 0.0f;
-#pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      if (c < nc) {
-        const float sc = (mv[c] == -__builtin_inff()) ? 0.0f : exp2f(mv[c] - mx);
-        lsum += lv[c] * sc;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] += xv[c][e] * sc;
-      }
-    }
-    const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) op[lane * PER + e] = f2bf(acc[e] * inv);
-    return;
-  }
-  float mx = -__builtin_inff();
-  for (int c0 = 0; c0 < nc; c0 += CG) {
-    float mv[CG];
-#pragma unroll
-    for (int c = 0; c < CG; ++c) mv[c] = c0 + c < nc ? pp[(c0 + c) * (HD + 2) + HD] : -__builtin_inff();
-#pragma unroll
-    for (int c = 0; c < CG; ++c) mx = fmaxf(mx, mv[c]);
-  }
+  const float *pp = a.part + (size_t)pair * MC * ATTN_PITCH(HD);
   float acc[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.0f;
-  float lsum = 0.0f;
-  for (int c0 = 0; c0 < nc; c0 += CG) {
-    float mv[CG], lv[CG], xv[CG][PER];
+  float mx = -__builtin_inff(), lsum = 0.0f;
+  for (int c0 = 0; c0 < nc; c0 += 32) {
+    const int cnt = min(32, nc - c0);
+    const float *p0 = pp + (size_t)c0 * ATTN_PITCH(HD);
+    float xv[CG][PER];
+    auto load = [&](int cc) {
 #pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      if (c0 + c < nc) {
-        const float *q = pp + (c0 + c) * (HD + 2);
-        mv[c] = q[HD];
-        lv[c] = q[HD + 1];
+      for (int u = 0; u < CG; ++u)
 #pragma unroll
-        for (int e = 0; e < PER; ++e) xv[c][e] = q[lane * PER + e];
+        for (int e = 0; e < PER; ++e) xv[u][e] = cc + u < cnt ? p0[(cc + u) * ATTN_PITCH(HD) + lane * PER + e] : 0.0f;
+    };
+    load(0);
+    const float mv = lane < cnt ? p0[lane * ATTN_PITCH(HD) + HD] : -__builtin_inff();
+    const float lv = lane < cnt ? p0[lane * ATTN_PITCH(HD) + HD + 1] : 0.0f;
+    float gm = mv;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) gm = fmaxf(gm, __shfl_xor(gm, off, 32));
+    const float mn = fmaxf(mx, gm), sub = mn == -__builtin_inff() ? 0.0f : mn;
+    const float w = __builtin_amdgcn_exp2f(mv - sub);         // 0 for an empty chunk
+    float ls = lv * w;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) ls += __shfl_xor(ls, off, 32);
+    const float old = __builtin_amdgcn_exp2f(mx - sub);
+    lsum = lsum * old + ls;
+    mx = mn;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] *= old;
+    for (int cc = 0;; cc += CG) {
+#pragma unroll
+      for (int u = 0; u < CG; ++u) {
+        const float wc = __shfl(w, cc + u, 32);
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] += xv[u][e] * wc;
       }
-    }
-#pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      if (c0 + c < nc) {
-        const float sc = (mv[c] == -__builtin_inff()) ? 0.0f : exp2f(mv[c] - mx);
-        lsum += lv[c] * sc;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] += xv[c][e] * sc;
-      }
+      if (cc + CG >= cnt) break;
+      load(cc + CG);
     }
   }
   const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+  uint16_t *op = a.out + (size_t)pair * HD + lane * PER;
 #pragma unroll
-  for (int e = 0; e < PER; ++e) op[lane * PER + e] = f2bf(acc[e] * inv);
+  for (int e = 0; e < PER; e += 2) *(uint32_t *)(op + e) = pack_bf2(acc[e] * inv, acc[e + 1] * inv);
 }
 
 template <int HD>
@@ -450,8 +425,8 @@ int launch_hd(const AttnArgs &a, int rows_max, const int32_t *packed_req, int wa
   } else {
     DCUT_TRY(launch(DCUT_KERNEL_ATTN, k_attn<HD, 16, 4, 1>, grid, dim3(1024), 0, s, a));
   }
-  int nw = rows_max * a.n_q;
-  return launch(DCUT_KERNEL_ATTN_COMBINE, k_attn_combine<HD>, dim3((nw + 3) / 4), dim3(256), 0, s, a,
+  if (a.max_chunks == 1) return DCUT_OK;      // every request is finished in place
+  return launch(DCUT_KERNEL_ATTN_COMBINE, k_attn_combine<HD>, dim3((rows_max * a.n_q + 7) / 8), dim3(256), 0, s, a,
                 packed_req, rows_max);
 }
 

@@ -240,6 +240,10 @@ size_t moe_ws_bytes(int M_max, int H, int E, int top_k, int inter);
 bool moe_supported(int M_max, int H, int E, int top_k);
 int moe_launch(const MoeArgs &m, hipStream_t s);
 
+// Floats per (row, head, chunk) attention partial: the values, then (max, sum),
+// padded to whole 16-byte units.
+__host__ __device__ constexpr int ATTN_PITCH(int head_dim) { return head_dim + 4; }
+
 struct AttnArgs {
   const uint16_t *q;        // [M][n_q][hd] bf16 (after RoPE)
   const uint16_t *kv_k, *kv_v;
@@ -247,7 +251,7 @@ struct AttnArgs {
   const int32_t *kv_cap;
   const int32_t *cu, *ctx_len;
   int B, D, n_q, n_kv, head_dim, chunk, max_chunks;
-  float *part;              // [M_max][n_q][max_chunks][hd + 2]
+  float *part;              // [M_max][n_q][max_chunks][ATTN_PITCH(hd)]
   uint16_t *out;            // [M][n_q][hd] bf16
   int32_t *dev_err;
   int32_t *plan;            // work-order scratch of attn_plan_bytes(B, n_kv, max_chunks), or null

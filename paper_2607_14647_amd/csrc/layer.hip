@@ -14,13 +14,18 @@
 
 namespace dcut {
 
-// Split-KV chunk length (cache keys per attention work item): 1024 keys when the
-// batch still gives at least 2048 work items, else 512.  A function of the
-// shapes only (B, n_kv, max_ctx), never of the kept rows, so a row's partial
-// sums never depend on the budget.
+// Split-KV chunk length (cache keys per attention work item).  1024 keys when the
+// batch still gives at least 2048 work items, else 512; a chunk is one workgroup's
+// serial loop, so the smallest batches, whose items would leave CUs idle, take 256
+// keys (up to 576 items, about two per CU) or 128 (up to 288).  Attention and merge
+// together, 8 kv heads, contexts of 2-4k: batch 1 28 us at 512 keys, 22 at 256, 20 at
+// 128; batch 4 28, 25 and 31; batch 8 32, 33 and 37.  A function of the shapes only
+// (B, n_kv, max_ctx), never of the kept rows, so a row's partial sums never depend on
+// the budget.
 static int attn_chunk(const dcut_layer_cfg *c, int B) {
-  const long long items = (long long)B * c->n_kv * ((c->max_ctx + 1023) / 1024);
-  return items >= 2048 ? 1024 : 512;
+  auto items = [&](int chunk) { return (long long)B * c->n_kv * ((c->max_ctx + chunk - 1) / chunk); };
+  if (items(1024) >= 2048) return 1024;
+  return items(128) <= 288 ? 128 : items(256) <= 576 ? 256 : 512;
 }
 
 struct LayerWs {
@@ -67,7 +72,7 @@ static LayerWs layer_ws(const dcut_layer_cfg *c, int B, int D) {
   w.q = off; off = align256(off + M * qd * 2);
   w.attn = off; off = align256(off + M * qd * 2);
   w.rope = off; off = align256(off + M * (c->head_dim / 2) * sizeof(float2));
-  w.part = off; off = align256(off + M * c->n_q * (size_t)mc * (c->head_dim + 2) * sizeof(float));
+  w.part = off; off = align256(off + M * c->n_q * (size_t)mc * ATTN_PITCH(c->head_dim) * sizeof(float));
   w.plan = off; off = align256(off + attn_plan_bytes(B, c->n_kv, mc));
   w.mid = off; off = align256(off + (c->n_exp == 0 ? M * (size_t)c->inter * 2 : 0));
   const size_t nqkv = (size_t)(c->n_q + 2 * c->n_kv) * c->head_dim;
