@@ -100,19 +100,27 @@ inline void allow_lds(Kernel kernel, size_t bytes) {
   }
 }
 
-// Launch `kernel`, recording the armed profiling events around it when `kid` is armed.
+// Launch `kernel`; when `kid` is armed, record the start event before it if it is
+// the `first` kernel of that id's work and the stop event after it if the `last`.
 template <typename Kernel, typename... Args>
-inline int launch(int kid, Kernel kernel, dim3 grid, dim3 block, size_t shmem, hipStream_t s,
-                  Args... args) {
+inline int launch_span(int kid, bool first, bool last, Kernel kernel, dim3 grid, dim3 block, size_t shmem,
+                       hipStream_t s, Args... args) {
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return DCUT_OK;
   allow_lds(kernel, shmem);
   ProfileHook &h = profile_hook();
   if (kid != DCUT_KERNEL_NONE && h.kernel == kid) {
-    hipExtLaunchKernelGGL(kernel, grid, block, shmem, s, h.start, h.stop, 0, args...);
+    hipExtLaunchKernelGGL(kernel, grid, block, shmem, s, first ? h.start : nullptr, last ? h.stop : nullptr, 0, args...);
   } else {
     hipLaunchKernelGGL(kernel, grid, block, shmem, s, args...);
   }
   return hipGetLastError() == hipSuccess ? DCUT_OK : DCUT_EHIP;
+}
+
+// Launch `kernel`, recording the armed profiling events around it when `kid` is armed.
+template <typename Kernel, typename... Args>
+inline int launch(int kid, Kernel kernel, dim3 grid, dim3 block, size_t shmem, hipStream_t s,
+                  Args... args) {
+  return launch_span(kid, true, true, kernel, grid, block, shmem, s, args...);
 }
 
 #define DCUT_TRY(expr)              \

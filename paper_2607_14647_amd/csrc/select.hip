@@ -4,15 +4,24 @@
 // packing of App. C; for rejection-sampling verification (App. B) the same
 // kernel ranks the shifted scores of Eq. dcut-shifted-score and chooses the
 // budget causally: by the early-stopping scan, or as a budget fixed beforehand.
-// One 1024-thread workgroup does it all, packing included: the whole problem is
-// at most 8192 positions (64 KB of sort keys in LDS), so a single workgroup
-// avoids any grid-wide synchronisation and launch round trips.
+// At most 8192 positions take part, so nothing here is bound by bytes or
+// operations but by serial chains and launches.  A position's place in the
+// ranking is the number of positions ahead of it, counted directly against every
+// other one: scores are read four at a time as LDS broadcasts and compared in 32
+// bits, which needs no sort network and no barrier, and splits over any number of
+// workgroups.  Up to 256 positions one 1024-thread workgroup does everything.
+// Above, the N^2 comparisons of one workgroup would take longer than a launch, so
+// a first kernel ranks 16 positions per workgroup over the whole chip and the second,
+// one workgroup, does the rest (prefix sums, budget choice, keep depths, packing).
+// Against sorting 64-key runs and merging them in one workgroup: 4096 positions
+// (batch 256) 50.2 -> 15.6 us (both kernels), 1024 (batch 64)
+// 19.2 -> 10.9, 64 (batch 4) 8.7 -> 7.5.
 //
 // Bit-exactness: each request's scores are one sequential float32 product per
-// depth (denormals kept, no contraction); ranking uses the unique 64-bit key
-// (score bits, 63 - depth, 65535 - request), so any correct sort gives the same
-// order; benefits are integer sums of trunc(s * 2^40); the budget objective is
-// one float64 division.  The outputs are therefore identical on any hardware.
+// depth (denormals kept, no contraction); the rank order (score descending, then
+// depth, then request) is total, so any correct count gives the same ranks;
+// benefits are integer sums of trunc(s * 2^40); the budget objective is one
+// float64 division.  The outputs are therefore identical on any hardware.
 #include "dcut_internal.h"
 #include "scan.h"
 
@@ -28,15 +37,9 @@ struct SelectParams {
   double costs[DCUT_MAX_CANDIDATES];
 };
 
-__device__ __forceinline__ unsigned long long rank_key(float s, int k, int i) {
-  return ((unsigned long long)__float_as_uint(s) << 32) |
-         ((unsigned long long)(63 - k) << 16) | (unsigned long long)(65535 - i);
-}
-
-// trunc(s * 2^40) for the score held in a key's upper half
-__device__ __forceinline__ unsigned long long key_units(unsigned long long key) {
-  float s = __uint_as_float((uint32_t)(key >> 32));
-  return (unsigned long long)((double)s * 1099511627776.0);
+// trunc(s * 2^40) for a score's bits
+__device__ __forceinline__ unsigned long long score_units(uint32_t bits) {
+  return (unsigned long long)((double)__uint_as_float(bits) * 1099511627776.0);
 }
 
 __device__ __forceinline__ bool conf_bad(float c) { return !(c >= 0.0f && c <= 1.0f) || signbit(c); }
@@ -67,144 +70,184 @@ __device__ __forceinline__ double objective(unsigned long long P, double cost) {
   return ((double)P * 0x1p-40) / cost;
 }
 
-__global__ void __launch_bounds__(1024)
-k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restrict__ draft,
-         const int32_t *__restrict__ ctx_len, int32_t *__restrict__ keep_len, int32_t *__restrict__ cu,
-         int32_t *__restrict__ ptok, int32_t *__restrict__ ppos, int32_t *__restrict__ preq,
-         int32_t *__restrict__ choice, unsigned long long *__restrict__ benefit,
-         int32_t *__restrict__ dev_err, int32_t *__restrict__ k_state) {
-  extern __shared__ unsigned long long smem[];
-  __shared__ unsigned long long s_wave[17];
-  __shared__ unsigned long long s_ben[DCUT_MAX_CANDIDATES];
-  __shared__ double s_cost[DCUT_MAX_CANDIDATES], s_obj[DCUT_MAX_CANDIDATES];
-  __shared__ int s_bud[DCUT_MAX_CANDIDATES];
-  __shared__ unsigned long long s_tau;
-  __shared__ int s_err, s_stop;
+constexpr int SEL_FUSED_MAX = 256;     // positions ranked by the one-workgroup kernel
+constexpr int RANK_THREADS = 512;
 
-  const int tid = threadIdx.x;
-  const int D = p.D, D1 = p.D + 1, B = p.B;
-  const int N = B * D1;
-  int NP = 64;
-  while (NP < N) NP <<= 1;
-  unsigned long long *keys = smem;          // [NP]
-  int *s_kl = (int *)smem;                  // [B], then s_cu [B+1]: the key area (and the prefix
-                                            // sums after it) once both are dead
-  int *s_cu = s_kl + B;
-  float *s_conf = (float *)(smem + NP + blockDim.x);   // [B * D], staged once (coalesced)
-  if (tid == 0) {
-    s_err = 0;
-    s_stop = N;
-  }
-  for (int j = tid; j < B * D; j += blockDim.x) s_conf[j] = conf[j];
-  if (tid < p.R) {
-    s_bud[tid] = p.budgets[tid];
-    s_cost[tid] = p.costs[tid];
-  }
+__host__ __device__ constexpr int pad64(int n) { return (n + 63) & ~63; }
+
+// Scores of every position, as bits, into sc[k * B + i] (depth, then request: the
+// order of ties), one thread per request, sequential in depth; zeros up to a
+// multiple of 64.  s_conf: B * D floats of LDS.  Returns whether a confidence was bad.
+__device__ __forceinline__ bool fill_scores(int B, int D, int shift, const float *__restrict__ conf, float *s_conf,
+                                            int *sc) {
+  const int N = B * (D + 1);
+  for (int j = threadIdx.x; j < B * D; j += blockDim.x) s_conf[j] = conf[j];
   __syncthreads();
-
-  // 1. scores and keys, one thread per request, sequential in depth
-  for (int i = tid; i < B; i += blockDim.x) {
+  bool bad = false;
+  for (int i = threadIdx.x; i < B; i += blockDim.x) {
     float s = 1.0f;
-    keys[i * D1] = rank_key(s, 0, i);
+    sc[i] = __float_as_int(s);
     for (int k = 1; k <= D; ++k) {
       float c = s_conf[i * D + (k - 1)];
       if (conf_bad(c)) {
-        s_err = 1;
+        bad = true;
         c = 0.0f;
       }
       const float prev = s;          // the shifted score of depth k: the product up to k - 1
       s = s * c;
-      keys[i * D1 + k] = rank_key(p.shift ? prev : s, k, i);
+      sc[k * B + i] = __float_as_int(shift ? prev : s);
     }
   }
-  for (int j = N + tid; j < NP; j += blockDim.x) keys[j] = 0ull;   // sorts last
-
-  // 2. sort, descending.  Each wave sorts 64-key runs in registers (a bitonic
-  // network over cross-lane shuffles, no barrier); then runs are merged
-  // pairwise: a key's place in the merged run is its index in its own run plus
-  // the number of keys ahead of it in the other run (a binary search; equal
-  // keys, which only the zero padding has, go left run first).
+  for (int j = N + threadIdx.x; j < pad64(N); j += blockDim.x) sc[j] = 0;
   __syncthreads();
-  {
-    const int lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
-    for (int run = wv; run < NP / 64; run += nwv) {
-      unsigned long long x = keys[run * 64 + lane];
+  return bad;
+}
+
+// Positions of the 16-position units [lo, hi) ahead of position m (in unit mu) in
+// the ranking: a larger score, or an equal one earlier in the order of ties (bits
+// of scores are below 2^31, so "at least s" is "more than s - 1").  The zeros that
+// pad the last units come after every position and are ahead of none.
+__device__ __forceinline__ int count_ahead(const int *sc, int mu, int m, int lo, int hi) {
+  const int s = sc[m];
+  int cnt = 0;
+  for (int u = lo; u < hi; ++u) {
+    const int4 *q = (const int4 *)(sc + 16 * u);
+    if (u == mu) {
+      for (int j = 0; j < 16; ++j) cnt += sc[16 * u + j] > s - (16 * u + j < m ? 1 : 0);
+    } else {
+      const int thr = s - (u < mu ? 1 : 0);
 #pragma unroll
-      for (int size = 2; size <= 64; size <<= 1)
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-          const unsigned long long y = __shfl_xor(x, stride, 64);
-          // the lower lane of a pair keeps the larger key in a descending run
-          const bool take_max = ((lane & stride) == 0) == ((lane & size) == 0);
-          x = take_max ? (x > y ? x : y) : (x < y ? x : y);
-        }
-      keys[run * 64 + lane] = x;
-    }
-    const int EM = NP > (int)blockDim.x ? NP / (int)blockDim.x : 1;   // keys per thread, <= 8
-    for (int width = 64; width < NP; width <<= 1) {
-      __syncthreads();
-      unsigned long long mine[8];
-      int dest[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (e >= EM) break;
-        const int idx = tid + e * (int)blockDim.x;
-        dest[e] = -1;
-        if (idx >= NP) continue;
-        const unsigned long long x = keys[idx];
-        const int base = idx & ~(2 * width - 1);
-        const bool left = idx - base < width;
-        const int own = idx - base - (left ? 0 : width);
-        const unsigned long long *other = keys + base + (left ? width : 0);
-        int lo = 0, hi = width;
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          const unsigned long long o = other[mid];
-          if (left ? (o > x) : (o >= x)) lo = mid + 1;
-          else hi = mid;
-        }
-        mine[e] = x;
-        dest[e] = base + own + lo;
+      for (int j = 0; j < 4; ++j) {
+        const int4 v = q[j];
+        cnt += (v.x > thr) + (v.y > thr) + (v.z > thr) + (v.w > thr);
       }
-      __syncthreads();
+    }
+  }
+  return cnt;
+}
+
+// Ranks of 16 positions per workgroup (enough workgroups for the whole chip from
+// 4096 positions on): sixteen lanes hold the positions, the four lane groups of each
+// wave count against different shares of the list.  Leaves the rank of position
+// k * B + i in `rank` and the score bits in rank order in `sorted` (both [N], packed
+// arrays of the call until the second kernel overwrites them).
+__global__ void __launch_bounds__(RANK_THREADS)
+k_select_rank(int B, int D, int shift, const float *__restrict__ conf, int32_t *__restrict__ rank,
+              int32_t *__restrict__ sorted, int32_t *__restrict__ dev_err) {
+  extern __shared__ __align__(16) int s_rank_mem[];
+  constexpr int NW = RANK_THREADS / 64;
+  __shared__ int s_cnt[NW][16];
+  const int N = B * (D + 1), NU = pad64(N) / 16;
+  int *sc = s_rank_mem;                                      // [pad64(N)], then the confidences
+  const bool bad = fill_scores(B, D, shift, conf, (float *)(sc + pad64(N)), sc);
+  if (bad && blockIdx.x == 0 && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
+  const int l16 = threadIdx.x & 15, seg = threadIdx.x >> 4, wv = threadIdx.x >> 6;
+  const int m = 16 * blockIdx.x + l16;
+  int cnt = count_ahead(sc, blockIdx.x, m, NU * seg / (4 * NW), NU * (seg + 1) / (4 * NW));
+  cnt += __shfl_xor(cnt, 16, 64);
+  cnt += __shfl_xor(cnt, 32, 64);
+  if ((threadIdx.x & 63) < 16) s_cnt[wv][l16] = cnt;
+  __syncthreads();
+  if (threadIdx.x < 16 && m < N) {
+    int r = 0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (e >= EM) break;
-        if (dest[e] >= 0) keys[dest[e]] = mine[e];
+    for (int w = 0; w < NW; ++w) r += s_cnt[w][l16];
+    rank[m] = r;
+    sorted[r] = sc[m];
+  }
+}
+
+// Everything after the ranking; with FUSED (N <= SEL_FUSED_MAX) the ranking too,
+// else ranks and sorted scores come from k_select_rank through ppos and ptok.
+template <bool FUSED>
+__global__ void __launch_bounds__(1024)
+k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restrict__ draft,
+         const int32_t *__restrict__ ctx_len, int32_t *__restrict__ keep_len, int32_t *__restrict__ cu,
+         int32_t *ptok, int32_t *ppos, int32_t *__restrict__ preq,
+         int32_t *__restrict__ choice, unsigned long long *__restrict__ benefit,
+         int32_t *__restrict__ dev_err, int32_t *__restrict__ k_state) {
+  extern __shared__ __align__(16) uint32_t s_mem[];
+  __shared__ unsigned long long s_wave[17], s_pre[1024];
+  __shared__ double s_cost[DCUT_MAX_CANDIDATES];
+  __shared__ int s_bud[DCUT_MAX_CANDIDATES];
+  __shared__ int s_stop, s_K;
+  constexpr int EM = FUSED ? 1 : DCUT_MAX_ROWS / 1024;    // positions per thread, at most
+
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int D1 = p.D + 1, B = p.B;
+  const int N = B * D1;
+  int *s_rank = (int *)s_mem;               // [N]: rank of position k * B + i
+  uint32_t *s_sort = s_mem + pad64(N);      // [N]: score bits in rank order
+  int *s_kl = (int *)(s_sort + pad64(N));   // [B], then s_cu [B + 1]
+  int *s_cu = s_kl + B;
+  if (tid == 0) s_stop = N;
+  if (tid < p.R) {
+    s_bud[tid] = p.budgets[tid];
+    s_cost[tid] = p.costs[tid];
+  }
+  // what the packing needs, fetched before the serial part
+  int zt[EM], zl[EM];
+#pragma unroll
+  for (int e = 0; e < EM; ++e) {
+    const int idx = tid + 1024 * e;
+    zt[e] = idx < N ? draft[idx] : 0;
+    zl[e] = idx < N ? ctx_len[idx / D1] : 0;
+  }
+  if constexpr (FUSED) {
+    // 1.-2. scores, and ranks: a wave per 16 positions, its lane groups sharing the list
+    int *sc = (int *)(((uintptr_t)(s_cu + B + 1) + 15) & ~(uintptr_t)15);
+    const bool bad = fill_scores(B, p.D, p.shift, conf, (float *)(sc + pad64(N)), sc);
+    if (bad && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
+    static_assert(SEL_FUSED_MAX <= 16 * 16, "one wave per 16 positions");
+    const int NU = pad64(N) / 16, seg = lane >> 4, m = 16 * wv + (lane & 15);
+    if (wv < NU) {
+      int cnt = count_ahead(sc, wv, m, NU * seg / 4, NU * (seg + 1) / 4);
+      cnt += __shfl_xor(cnt, 16, 64);
+      cnt += __shfl_xor(cnt, 32, 64);
+      if (lane < 16 && m < N) {
+        s_rank[m] = cnt;
+        s_sort[cnt] = (uint32_t)sc[m];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EM; ++e) {
+      const int j = tid + 1024 * e;
+      if (j < N) {
+        s_rank[j] = ppos[j];
+        s_sort[j] = (uint32_t)ptok[j];
       }
     }
   }
   __syncthreads();
 
   // 3. exact prefix sums of the fixed-point scores in rank order
-  const int E = NP > (int)blockDim.x ? NP / (int)blockDim.x : 1;   // ranks per thread
+  const int E = (N + 1023) / 1024;          // ranks per thread
   unsigned long long local = 0;
   for (int m = tid * E; m < tid * E + E; ++m)
-    if (m < N) local += key_units(keys[m]);
+    if (m < N) local += score_units(s_sort[m]);
   unsigned long long total;
-  unsigned long long pre = block_exclusive_scan(local, s_wave, &total);
-  unsigned long long *s_pre = smem + NP;    // [blockDim.x]
+  const unsigned long long pre = block_exclusive_scan(local, s_wave, &total);
   s_pre[tid] = pre;
   __syncthreads();
+  double obj = -1.0;                        // candidate tid's objective (first wave)
   if (tid < p.R) {
-    int K = p.budgets[tid];
-    int t = K / E, rem = K - t * E;
-    unsigned long long P = (t < (int)blockDim.x) ? s_pre[t] : total;
-    for (int m = t * E; m < t * E + rem; ++m) P += key_units(keys[m]);
-    s_ben[tid] = P;
-    s_obj[tid] = objective(P, s_cost[tid]);   // every candidate's objective at once
+    const int K = s_bud[tid];
+    const int t = K / E, rem = K - t * E;
+    unsigned long long P = t < 1024 ? s_pre[t] : total;
+    for (int m = t * E; m < t * E + rem; ++m) P += score_units(s_sort[m]);
+    obj = objective(P, s_cost[tid]);
     if (benefit) benefit[tid] = P;
   }
-  __syncthreads();
 
   // 4a. causal scan (App. B): the positions enter in rank order from K = B on,
   // and the scan stops at the first K whose next position does not strictly
   // raise the objective.  Every thread tests the sizes of its own ranks.
   if (p.mode == SEL_SCAN) {
-    unsigned long long P = s_pre[tid];          // benefit of the first tid * E ranks
+    unsigned long long P = pre;             // benefit of the first tid * E ranks
     int stop = N;
     for (int m = tid * E; m < tid * E + E && m < N; ++m) {
-      const unsigned long long P1 = P + key_units(keys[m]);
+      const unsigned long long P1 = P + score_units(s_sort[m]);
       if (m >= B && !(objective(P1, cost_at(s_bud, s_cost, p.R, m + 1)) >
                       objective(P, cost_at(s_bud, s_cost, p.R, m)))) {
         stop = m;
@@ -213,70 +256,68 @@ k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restri
       P = P1;
     }
     if (stop < N) atomicMin(&s_stop, stop);
+    __syncthreads();
   }
-  __syncthreads();
 
   // 4b. budget choice: the first strict maximum of benefit * 2^-40 / cost over
   // the candidates, the fixed budget, the scan's stop, or the budget carried
   // over from the previous block (which then carries this block's choice on)
-  if (tid == 0) {
-    int best = 0, Kstar;
-    int bucket = 0;                   // first strict maximum of the objective over the candidates
-    double best_obj = -1.0;
-    for (int r = 0; r < p.R; ++r) {
-      const double obj = s_obj[r];
-      if (obj > best_obj) {
-        best_obj = obj;
-        bucket = r;
+  if (wv == 0) {
+    static_assert(DCUT_MAX_CANDIDATES <= 64, "one candidate per lane");
+    double best_obj = obj;
+    int bucket = lane;                      // the largest objective, the smaller index among equals
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double o = __shfl_xor(best_obj, off, 64);
+      const int q = __shfl_xor(bucket, off, 64);
+      if (o > best_obj || (o == best_obj && q < bucket)) {
+        best_obj = o;
+        bucket = q;
       }
     }
-    if (p.mode == SEL_BUCKETS) {
-      best = bucket;
-      Kstar = p.budgets[best];
-    } else if (p.mode == SEL_FIXED) {
-      Kstar = p.budgets[0];
-    } else {
-      if (p.mode == SEL_SCAN) {
-        Kstar = s_stop;
+    if (lane == 0) {
+      int best = bucket, Kstar;
+      if (p.mode == SEL_BUCKETS) {
+        Kstar = s_bud[best];
+      } else if (p.mode == SEL_FIXED) {
+        best = 0;
+        Kstar = s_bud[0];
       } else {
-        const int k = k_state[0];
-        Kstar = k < B ? B : (k > N ? N : k);
-        k_state[0] = p.budgets[bucket];
+        if (p.mode == SEL_SCAN) {
+          Kstar = s_stop;
+        } else {
+          const int k = k_state[0];
+          Kstar = k < B ? B : (k > N ? N : k);
+          k_state[0] = s_bud[bucket];
+        }
+        best = -1;                          // the last candidate budget not above K*
+        for (int r = 0; r < p.R; ++r)
+          if (s_bud[r] <= Kstar) best = r;
       }
-      best = -1;                      // the last candidate budget not above K*
-      for (int r = 0; r < p.R; ++r)
-        if (p.budgets[r] <= Kstar) best = r;
+      choice[0] = Kstar;
+      choice[1] = best;
+      s_K = Kstar;
     }
-    choice[0] = Kstar;
-    choice[1] = best;
-    s_tau = keys[Kstar - 1];          // the K*-th largest key
-    if (s_err && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
   }
   __syncthreads();
 
-  // 5. keep depths: a request keeps the depths whose key ranks within the top K*
-  const unsigned long long tau = s_tau;
-  for (int i = tid; i < B; i += blockDim.x) {
-    float s = 1.0f;
-    int n = 1;                        // the bonus key (s = 1, k = 0) always ranks first in its request
-    for (int k = 1; k <= D; ++k) {
-      float c = s_conf[i * D + (k - 1)];
-      if (conf_bad(c)) c = 0.0f;
-      const float prev = s;
-      s = s * c;
-      if (rank_key(p.shift ? prev : s, k, i) >= tau) n = k + 1;
-      else break;
+  // 5. keep depths: request i keeps the depths ranked within the top K* (a prefix;
+  // its bonus position always is), so its last one sets the count
+  const int K = s_K;
+#pragma unroll
+  for (int e = 0; e < EM; ++e) {
+    const int j = tid + 1024 * e;
+    if (j < N && s_rank[j] < K && (j + B >= N || s_rank[j + B] >= K)) {
+      const int k = j / B;
+      s_kl[j - k * B] = k + 1;
+      keep_len[j - k * B] = k + 1;
     }
-    if (rank_key(1.0f, 0, i) < tau) n = 0;   // impossible when K* >= B; kept for safety
-    keep_len[i] = n;
-    s_kl[i] = n;
   }
   __syncthreads();
 
   // 6. packing (App. C): cu = exclusive scan of keep_len; row t = cu[i] + k
-  // gets (z_{i,k}, L_i + k, i).  The sort keys are dead by now; their LDS holds
-  // the offsets.
-  const int per = (B + blockDim.x - 1) / blockDim.x;   // <= 4
+  // gets (z_{i,k}, L_i + k, i), rows past K* zeros
+  const int per = (B + 1023) / 1024;        // <= 4
   int v[4];
   int loc = 0;
   for (int j = 0; j < per; ++j) {
@@ -288,19 +329,32 @@ k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restri
   int off = block_exclusive_scan(loc, (int *)s_wave, &kept);
   for (int j = 0; j < per; ++j) {
     const int i = tid * per + j;
-    if (i < B) s_cu[i] = off;
+    if (i < B) {
+      s_cu[i] = off;
+      cu[i] = off;
+    }
     off += v[j];
   }
-  if (tid == 0) s_cu[B] = kept;
+  if (tid == 0) {
+    s_cu[B] = kept;
+    cu[B] = kept;
+  }
   __syncthreads();
-  for (int i = tid; i <= B; i += blockDim.x) cu[i] = s_cu[i];
-  for (int idx = tid; idx < N; idx += blockDim.x) {
+#pragma unroll
+  for (int e = 0; e < EM; ++e) {
+    const int idx = tid + 1024 * e;
+    if (idx >= N) break;
     const int i = idx / D1, k = idx - i * D1;
-    if (k < s_cu[i + 1] - s_cu[i]) {
-      const int t = s_cu[i] + k;
-      ptok[t] = draft[idx];
-      ppos[t] = ctx_len[i] + k;
+    const int t = s_cu[i] + k;
+    if (t < s_cu[i + 1]) {
+      ptok[t] = zt[e];
+      ppos[t] = zl[e] + k;
       preq[t] = i;
+    }
+    if (idx >= kept) {
+      ptok[idx] = 0;
+      ppos[idx] = 0;
+      preq[idx] = 0;
     }
   }
 }
@@ -337,12 +391,18 @@ static int select_run(int B, int D, const float *conf, const int32_t *draft, con
     p.budgets[r] = K;
     p.costs[r] = c;
   }
-  int N = B * (D + 1), NP = 64;
-  while (NP < N) NP <<= 1;
-  size_t shmem = (size_t)(NP + 1024) * sizeof(unsigned long long) + (size_t)B * D * sizeof(float);
-  return launch(DCUT_KERNEL_SELECT, k_select, dim3(1), dim3(1024), shmem, stream, p, conf, draft, ctx_len,
-                keep_len, cu, packed_tok, packed_pos, packed_req, choice, (unsigned long long *)benefit, dev_err,
-                k_state);
+  const int N = B * (D + 1);
+  const size_t base = ((size_t)2 * pad64(N) + 2 * B + 1) * sizeof(uint32_t);   // ranks, sorted scores, keep depths, offsets
+  const size_t scores = (size_t)pad64(N) * sizeof(uint32_t) + (size_t)B * D * sizeof(float);
+  if (N <= SEL_FUSED_MAX)
+    return launch(DCUT_KERNEL_SELECT, k_select<true>, dim3(1), dim3(1024), base + 16 + scores, stream, p, conf, draft,
+                  ctx_len, keep_len, cu, packed_tok, packed_pos, packed_req, choice, (unsigned long long *)benefit,
+                  dev_err, k_state);
+  DCUT_TRY(launch_span(DCUT_KERNEL_SELECT, true, false, k_select_rank, dim3(pad64(N) / 16), dim3(RANK_THREADS), scores,
+                       stream, B, D, shift, conf, packed_pos, packed_tok, dev_err));
+  return launch_span(DCUT_KERNEL_SELECT, false, true, k_select<false>, dim3(1), dim3(1024), base, stream, p, conf, draft,
+                     ctx_len, keep_len, cu, packed_tok, packed_pos, packed_req, choice, (unsigned long long *)benefit,
+                     dev_err, k_state);
 }
 
 extern "C" int dcut_select(int B, int D, const float *conf, const int32_t *draft,
