@@ -182,7 +182,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, lo
                                            (int)(bytes < 0x7fffffffLL ? bytes : 0x7fffffffLL), 0x00020000);
 }
 
-template <int EPI, class T>
+template <int EPI, class T, int WPOL, bool GROUPED = false>
 __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   constexpr int GN = T::GN, WM = T::WM, WN = T::WN, NWV = T::NWV;
   constexpr int TM = T::TM, TN = T::TN, NA = T::NA, NB = T::NB;
@@ -202,7 +202,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 
   // live tasks: (row tile, column tile, split), row tile fastest, split slowest
   const int M = min(__builtin_amdgcn_readfirstlane(*a.m_count), a.M_max);
-  const unsigned nMT = a.tiles ? __builtin_amdgcn_readfirstlane(*a.n_tiles) : (M + TM - 1) / TM;
+  const unsigned nMT = GROUPED ? __builtin_amdgcn_readfirstlane(*a.n_tiles) : (M + TM - 1) / TM;
   const unsigned nNT = n_col_tiles<EPI>(a, TN);
   const int splits = a.splits > 1 ? a.splits : 1;
   const unsigned ntask = nMT * nNT * splits;
@@ -229,10 +229,11 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   const uint32_t fragW = lds0 + NA * ASTAGE + wn * WN * 4096 + frow;
 
   for (unsigned task = lo + (blockIdx.x >> 3); task < hi; task += per_xcd) {
-    const unsigned rest = task / nMT;
-    const unsigned mt = task - rest * nMT;
+    // grouped: column tile fastest, so an expert's rows are read by its column tiles at once
+    const unsigned rest = GROUPED ? task : task / nMT;
+    const unsigned mt = GROUPED ? task / nNT : task - rest * nMT;
     const unsigned sp = splits > 1 ? rest / nNT : 0;
-    const unsigned nt = rest - sp * nNT;
+    const unsigned nt = GROUPED ? task - mt * nNT : rest - sp * nNT;
     int m0 = mt * TM, Mlim = M;
     const uint16_t *Wb = a.W;
     const int kt0 = sp * per_split;
@@ -243,7 +244,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     // split-K the splits start apart already (a shift on top measured no faster).
     // Logits all start at k = 0: equal weight rows have to give equal logits.
     int rot = 0;
-    if (a.tiles) {
+    if constexpr (GROUPED) {
       // uniform, but loaded through the vector path: kept scalar
       const int e = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt]);
       m0 = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt + 1]);
@@ -258,7 +259,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     // up rows; a head's first group is its first 32 dimensions)
     const int wrow0 = max(group_wrow<EPI>(a, grp0), 0);
     const __amdgpu_buffer_rsrc_t rsW = make_rsrc(Wb + (size_t)wrow0 * a.ldw, (long long)(w_rows_ext - wrow0) * a.ldw * 2);
-    const bool gather = a.a_rows != nullptr;
+    const bool gather = GROUPED && a.a_rows != nullptr;
     const __amdgpu_buffer_rsrc_t rsA =
         gather ? make_rsrc(a.A, (long long)a.a_extent * a.lda * 2)
                : make_rsrc(a.A + (size_t)m0 * a.lda, (long long)(Mlim - m0) * a.lda * 2);
@@ -301,7 +302,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     };
     auto issueW = [&](int j, int koff, unsigned kill, uint32_t stage) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lds_void *)(uintptr_t)(lds0 + NA * ASTAGE + stage + (wave + NWV * j) * 1024),
-                                               16, boff[j] | kill, koff, 0, 0);
+                                               16, boff[j] | kill, koff, 0, WPOL);
     };
 
     floatx16 acc[WM][WN];
@@ -633,10 +634,10 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   }
 }
 
-template <int EPI, class T>
+template <int EPI, class T, int WPOL, bool GROUPED>
 __global__ void __launch_bounds__(T::THREADS)
 k_gemm(GemmArgs a) {
-  gemm_tasks<EPI, T>(a);
+  gemm_tasks<EPI, T, WPOL, GROUPED>(a);
 }
 
 // Dense GEMM whose tile shape follows the live row count M (read on the device):
@@ -646,7 +647,7 @@ k_gemm(GemmArgs a) {
 // last 256-row tile would be at most half full.  Every element is the
 // same sequence of MFMA k-steps in both shapes, so the choice never changes a
 // result bit.
-template <int EPI>
+template <int EPI, int WPOL>
 __global__ void __launch_bounds__(Big::THREADS)
 k_gemm_dual(GemmArgs a) {
   static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for both tiles");
@@ -657,11 +658,11 @@ k_gemm_dual(GemmArgs a) {
     const long long nct = n_col_tiles<EPI>(a, Big::TN), G = gridDim.x;
     const long long big_rounds = ((M + Big::TM - 1) / Big::TM * nct + G - 1) / G;
     const long long mid_rounds = ((M + Mid::TM - 1) / Mid::TM * nct + G - 1) / G;
-    if (mid_rounds < 2 * big_rounds) gemm_tasks<EPI, Mid>(a);
-    else gemm_tasks<EPI, Big>(a);
+    if (mid_rounds < 2 * big_rounds) gemm_tasks<EPI, Mid, WPOL>(a);
+    else gemm_tasks<EPI, Big, WPOL>(a);
   } else {
-    if (lm_head_mid_tile(M)) gemm_tasks<EPI, MidDeep>(a);
-    else gemm_tasks<EPI, Big>(a);
+    if (lm_head_mid_tile(M)) gemm_tasks<EPI, MidDeep, WPOL>(a);
+    else gemm_tasks<EPI, Big, WPOL>(a);
   }
 }
 
@@ -759,7 +760,7 @@ int cu_count() {
 // 16 rows QKV 17.2 -> 14.4 us and O 15.1 -> 13.5 against a two-slice lead; from 128
 // rows on both leads measured the same.  Every element is the same sequence of MFMA
 // k-steps in all of them.
-template <int EPI>
+template <int EPI, int WPOL>
 __device__ __forceinline__ void gemm_by_rows(const GemmArgs &a) {
   const unsigned M = min(*a.m_count, a.M_max), G = gridDim.x, sp = a.splits > 1 ? a.splits : 1;
   auto cost = [&](unsigned tm, unsigned tn, unsigned w) {
@@ -769,22 +770,22 @@ __device__ __forceinline__ void gemm_by_rows(const GemmArgs &a) {
   // without split-K the RoPE epilogue needs both halves of a pair in one wave (two column
   // groups), which the 128 x 128 tile's waves do not have
   const bool paired = EPI == EPI_QKV_ROPE && sp == 1;
-  if (!paired && deep <= mid && deep <= big) gemm_tasks<EPI, Deep>(a);
-  else if (mid <= big) gemm_tasks<EPI, Mid>(a);
-  else gemm_tasks<EPI, Big>(a);
+  if (!paired && deep <= mid && deep <= big) gemm_tasks<EPI, Deep, WPOL>(a);
+  else if (mid <= big) gemm_tasks<EPI, Mid, WPOL>(a);
+  else gemm_tasks<EPI, Big, WPOL>(a);
 }
 
-template <int EPI>
+template <int EPI, int WPOL>
 __global__ void __launch_bounds__(Big::THREADS)
 k_gemm_f32(GemmArgs a) {
   static_assert(Deep::THREADS == Big::THREADS && Deep::LDS <= Big::LDS, "one launch shape for all tiles");
   static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for all tiles");
-  gemm_by_rows<EPI>(a);
+  gemm_by_rows<EPI, WPOL>(a);
 }
 
-template <int EPI, class T>
+template <int EPI, class T, int WPOL, bool GROUPED = false>
 int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
-  const int nMT = a.tiles ? a.m_tiles : (a.M_max + T::TM - 1) / T::TM;
+  const int nMT = GROUPED ? a.m_tiles : (a.M_max + T::TM - 1) / T::TM;
   const int nNT = EPI == EPI_SWIGLU ? (a.swiglu_inter + T::TN / 2 - 1) / (T::TN / 2) : (a.N + T::TN - 1) / T::TN;
   if (a.splits > 1) return DCUT_EINVAL;
   if ((EPI == EPI_ARGMAX || EPI == EPI_SAMPLE) && (!a.amax_keys || a.amax_slots < nNT * T::GN))
@@ -796,12 +797,12 @@ int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
   if (g < 8) g = 8;
-  return launch(kid, k_gemm<EPI, T>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
+  return launch(kid, k_gemm<EPI, T, WPOL, GROUPED>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
 }
 
 // k_gemm_f32 and, with split-K, the pass that adds the partials (unless the
 // caller does).  One workgroup per CU, fewer when the 128 x 128 tasks are fewer.
-template <int EPI>
+template <int EPI, int WPOL>
 int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
   const int splits = a.splits > 1 ? a.splits : 1;
   if (splits > 1 && (!a.split_part || a.N % 4 || (EPI != EPI_QKV_ROPE && a.ldo % 4))) return DCUT_EINVAL;
@@ -809,7 +810,7 @@ int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
   long long g = cu_count();
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
-  DCUT_TRY(launch(kid, k_gemm_f32<EPI>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a));
+  DCUT_TRY(launch(kid, k_gemm_f32<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a));
   if (splits == 1 || a.defer_reduce) return DCUT_OK;
   if (EPI == EPI_QKV_ROPE) {
     const int quads = (a.n_q + 2 * a.n_kv) * (a.head_dim / 8);
@@ -824,28 +825,47 @@ int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
 // their tile on the device (k_gemm_f32).  The others: Big tiles with at least one
 // Big tile per CU at M_max rows (the SwiGLU and LM-head GEMMs pick Big or a
 // 128-row tile on the device from the live rows), Small tiles below that.
-template <int EPI>
-int launch_epi(int kid, const GemmArgs &a, hipStream_t s) {
-  if (a.tiles) return launch_tile<EPI, Small>(kid, a, s);
+template <int EPI, int WPOL>
+int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
+  if (a.tiles) {
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_STORE_F32) return launch_tile<EPI, Small, WPOL, true>(kid, a, s);
+    else return DCUT_EINVAL;
+  }
   if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE) {
-    return launch_f32<EPI>(kid, a, s);
+    return launch_f32<EPI, WPOL>(kid, a, s);
   } else {
     const long long big_tasks = (long long)((a.M_max + Big::TM - 1) / Big::TM) *
         (EPI == EPI_SWIGLU ? (a.swiglu_inter + Big::TN / 2 - 1) / (Big::TN / 2) : (a.N + Big::TN - 1) / Big::TN);
-    if (big_tasks < cu_count()) return launch_tile<EPI, Small>(kid, a, s);
+    if (big_tasks < cu_count()) return launch_tile<EPI, Small, WPOL>(kid, a, s);
     if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX) {
       // tile shape chosen on the device from the live row count (one workgroup per CU);
       // the sampling epilogue keeps the 256-row tile (both paths in one kernel would spill)
       if (EPI == EPI_ARGMAX && (!a.amax_keys || a.amax_slots < (a.N + MidDeep::TN - 1) / MidDeep::TN * MidDeep::GN))
         return DCUT_EINVAL;
       const int g = (cu_count() + 7) / 8 * 8;
-      return launch(kid, k_gemm_dual<EPI>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
+      return launch(kid, k_gemm_dual<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
     } else if constexpr (EPI == EPI_SAMPLE) {
-      return launch_tile<EPI, BigFlat>(kid, a, s);
+      return launch_tile<EPI, BigFlat, WPOL>(kid, a, s);
     } else {
-      return launch_tile<EPI, Big>(kid, a, s);
+      return launch_tile<EPI, Big, WPOL>(kid, a, s);
     }
   }
+}
+
+// Cache policy of the weight loads.  A matrix of 64 MB or more is streamed
+// (non-temporal): it is gone from the 256 MB memory-side cache before its next use,
+// and without the policy it takes the activations, partials and caches of the layer
+// with it.  Gate-up 4096 x 28672 at 16, 128 and 256 rows 45 -> 43, 56 -> 50 and
+// 71 -> 66 us, the whole batch-16 layer 179 -> 163; LM head 4096 x 128256 at 64 rows
+// 201 -> 187; at 1024 rows all the same.  Smaller ones (QKV 5120 x 2048 of a MoE
+// layer: 12.4 us by default, 13.9 streamed) may still be there.  Expert weights stream
+// at any size: a step's rows read most experts, 128 of them 1.2 GB (gate-up at 768
+// rows 176 -> 142 us, down 94 -> 88).
+template <int EPI>
+int launch_epi(int kid, const GemmArgs &a, hipStream_t s) {
+  const long long w_rows = EPI == EPI_SWIGLU ? 2LL * a.swiglu_inter : a.N;
+  if (a.tiles || w_rows * a.ldw * 2 >= (64LL << 20)) return launch_policy<EPI, CPOL_NT>(kid, a, s);
+  return launch_policy<EPI, 0>(kid, a, s);
 }
 
 }  // namespace
