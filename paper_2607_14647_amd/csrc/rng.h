@@ -45,15 +45,18 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
 // 2^-19).  t so keeps its relative accuracy as u approaches 1, where the
 // largest variates come from.  Both branches share one logarithm and are
 // selected per lane, so lanes never diverge, and nothing divides.
-__device__ __forceinline__ float gumbel_of(uint32_t w) {
+__device__ __forceinline__ float neg_log_of(uint32_t w) {   // t
   constexpr float LN2 = 0.6931471805599453f;
   const bool lo = w < 0x80000000u;
   const float u = ((float)w + 0.5f) * 0x1p-32f;
   const float x = ((float)(0xffffffffu - w) + 0.5f) * 0x1p-32f;
   const float l = __log2f(lo ? u : 1.0f - x) * LN2;    // one logarithm for either branch
   const float s = x * (1.0f + x * (0.5f + x * (1.0f / 3.0f + x * 0.25f)));
-  const float t = (lo || x >= 0x1p-5f) ? -l : s;
-  return -__log2f(t) * LN2;
+  return (lo || x >= 0x1p-5f) ? -l : s;
+}
+__device__ __forceinline__ float gumbel_of(uint32_t w) {
+  constexpr float LN2 = 0.6931471805599453f;
+  return -__log2f(neg_log_of(w)) * LN2;
 }
 
 // Uniform on (0, 1) from one Philox output word: (w + 0.5) / 2^32 in float64.
