@@ -228,22 +228,57 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   const uint32_t fragA = lds0 + wm * WM * 4096 + frow;
   const uint32_t fragW = lds0 + NA * ASTAGE + wn * WN * 4096 + frow;
 
-  for (unsigned task = lo + (blockIdx.x >> 3); task < hi; task += per_xcd) {
+  // One task's position and operand addresses; setup() fills them and starts the
+  // task's first loads.
+  int m0, Mlim, grp0, kt0, nk, rot;
+  unsigned sp, nt;
+  __amdgpu_buffer_rsrc_t rsA, rsW;
+  unsigned aoff[AJ], boff[BJ];
+  // The k offset of a slice goes in the scalar offset; the per-lane offsets
+  // stay fixed over the k loop.  `kill` is zero, or OOB for a slice past the
+  // task's last (issued all the same, so that the count of loads in flight
+  // stays constant) and for chunks beyond K in a slice that reaches past it.
+  auto slice = [&](int it, unsigned &kill) {
+    const int q = it + rot;
+    const int k0 = (kt0 + (q >= nk ? q - nk : q)) * TK;
+    kill = ((unsigned)(it >= nk) | (unsigned)(kchunk >= a.K - k0)) << 31;
+    return k0 * 2;
+  };
+  auto issueA = [&](int j, int koff, unsigned kill, uint32_t stage) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void *)(uintptr_t)(lds0 + stage + (wave + NWV * j) * 1024), 16,
+                                             aoff[j] | kill, koff, 0, 0);
+  };
+  auto issueW = [&](int j, int koff, unsigned kill, uint32_t stage) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lds_void *)(uintptr_t)(lds0 + NA * ASTAGE + stage + (wave + NWV * j) * 1024),
+                                             16, boff[j] | kill, koff, 0, WPOL);
+  };
+  constexpr int PA = NA - 1, PW = NB - 1;   // slices in flight ahead of the one multiplied
+  constexpr int PMAX = PA > PW ? PA : PW;
+  static_assert(PW >= PA, "W runs at least as far ahead as A");
+  constexpr int NL = AJ + BJ, NM = TK / 16 * WM * WN;   // loads and MFMAs per slice
+  // loads issued after A[it] and W[it] were, when iteration `it` needs them:
+  // the W loads of A[it]'s own iteration (when W runs further ahead) and the
+  // iterations in between
+  constexpr int PEND = (PW > PA ? BJ : 0) + (PA - 1) * NL;
+  static_assert(PMAX * NL <= 63, "outstanding loads within the vmcnt range");
+
+  auto setup = [&](unsigned task) {
     // grouped: column tile fastest, so an expert's rows are read by its column tiles at once
     const unsigned rest = GROUPED ? task : task / nMT;
     const unsigned mt = GROUPED ? task / nNT : task - rest * nMT;
-    const unsigned sp = splits > 1 ? rest / nNT : 0;
-    const unsigned nt = GROUPED ? task - mt * nNT : rest - sp * nNT;
-    int m0 = mt * TM, Mlim = M;
+    sp = splits > 1 ? rest / nNT : 0;
+    nt = GROUPED ? task - mt * nNT : rest - sp * nNT;
+    m0 = mt * TM;
+    Mlim = M;
     const uint16_t *Wb = a.W;
-    const int kt0 = sp * per_split;
-    const int nk = max(0, min(nk_all, kt0 + per_split) - kt0);
-    const int grp0 = nt * (TN / 32);
+    kt0 = sp * per_split;
+    nk = max(0, min(nk_all, kt0 + per_split) - kt0);
+    grp0 = nt * (TN / 32);
     // First slice of the k loop: spread over the column eighths, or, for grouped
     // tasks (each reads weights of its own), over experts and column tiles.  With
     // split-K the splits start apart already (a shift on top measured no faster).
     // Logits all start at k = 0: equal weight rows have to give equal logits.
-    int rot = 0;
+    rot = 0;
     if constexpr (GROUPED) {
       // uniform, but loaded through the vector path: kept scalar
       const int e = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt]);
@@ -258,17 +293,15 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     // the lowest W row of the tile: its first column group (gate rows precede
     // up rows; a head's first group is its first 32 dimensions)
     const int wrow0 = max(group_wrow<EPI>(a, grp0), 0);
-    const __amdgpu_buffer_rsrc_t rsW = make_rsrc(Wb + (size_t)wrow0 * a.ldw, (long long)(w_rows_ext - wrow0) * a.ldw * 2);
+    rsW = make_rsrc(Wb + (size_t)wrow0 * a.ldw, (long long)(w_rows_ext - wrow0) * a.ldw * 2);
     const bool gather = GROUPED && a.a_rows != nullptr;
-    const __amdgpu_buffer_rsrc_t rsA =
-        gather ? make_rsrc(a.A, (long long)a.a_extent * a.lda * 2)
+    rsA = gather ? make_rsrc(a.A, (long long)a.a_extent * a.lda * 2)
                : make_rsrc(a.A + (size_t)m0 * a.lda, (long long)(Mlim - m0) * a.lda * 2);
 
     // Byte offsets of this lane's loads at k = 0.  Rows past the operand lie
     // beyond the buffer (A: Mlim ends it; W: the last row does, and the last
     // gate rows of an odd tile read up rows that no output uses) and read as
     // zeros; gathered rows past Mlim get an offset beyond it.
-    unsigned aoff[AJ], boff[BJ];
     if (gather) {
       int src[AJ];
 #pragma unroll
@@ -286,25 +319,33 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
       const int wr = group_wrow<EPI>(a, grp0 + (blk >> 2));
       boff[j] = wr < 0 ? OOB : (unsigned)((wr - wrow0 + RPI * (blk & 3) + lr) * a.ldw + kchunk) * 2;
     }
-    // The k offset of a slice goes in the scalar offset; the per-lane offsets
-    // stay fixed over the k loop.  `kill` is zero, or OOB for a slice past the
-    // task's last (issued all the same, so that the count of loads in flight
-    // stays constant) and for chunks beyond K in a slice that reaches past it.
-    auto slice = [&](int it, unsigned &kill) {
-      const int r = it + rot;
-      const int k0 = (kt0 + (r >= nk ? r - nk : r)) * TK;
-      kill = ((unsigned)(it >= nk) | (unsigned)(kchunk >= a.K - k0)) << 31;
-      return k0 * 2;
-    };
-    auto issueA = [&](int j, int koff, unsigned kill, uint32_t stage) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void *)(uintptr_t)(lds0 + stage + (wave + NWV * j) * 1024), 16,
-                                               aoff[j] | kill, koff, 0, 0);
-    };
-    auto issueW = [&](int j, int koff, unsigned kill, uint32_t stage) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lds_void *)(uintptr_t)(lds0 + NA * ASTAGE + stage + (wave + NWV * j) * 1024),
-                                               16, boff[j] | kill, koff, 0, WPOL);
-    };
+    // prologue: A[0 .. PA-1] and W[0 .. PW-1], interleaved by slice
+#pragma unroll
+    for (int q = 0; q < PMAX; ++q) {
+      unsigned kill;
+      const int koff = slice(q, kill);
+      if (q < PA) {
+#pragma unroll
+        for (int j = 0; j < AJ; ++j) issueA(j, koff, kill, q * ASTAGE);
+      }
+      if (q < PW) {
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) issueW(j, koff, kill, q * WSTAGE);
+      }
+    }
+  };
 
+  // The argmax LM head requests the next task's first slices before this one's
+  // epilogue, which hides their latency (768 rows of 2048 x 151936, seven tasks per
+  // CU: 397 -> 388 us; 1024 rows of 4096 x 128256: 833 -> 820).  They go to the stages
+  // 0 .. PA-1 and 0 .. PW-1; the epilogue uses the last stage of W, which the next task
+  // fills only after its first barrier.  The other GEMMs have one or two tasks per CU
+  // and lost up to 0.9 % to the registers it holds (sampling LM head 320 -> 323).
+  constexpr bool EARLY = EPI == EPI_ARGMAX;
+  unsigned task = lo + (blockIdx.x >> 3);
+  if (EARLY && task < hi) setup(task);
+  while (task < hi) {
+    if (!EARLY) setup(task);
     floatx16 acc[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -313,29 +354,6 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    constexpr int PA = NA - 1, PW = NB - 1;   // slices in flight ahead of the one multiplied
-    constexpr int PMAX = PA > PW ? PA : PW;
-    static_assert(PW >= PA, "W runs at least as far ahead as A");
-    constexpr int NL = AJ + BJ, NM = TK / 16 * WM * WN;   // loads and MFMAs per slice
-    // loads issued after A[it] and W[it] were, when iteration `it` needs them:
-    // the W loads of A[it]'s own iteration (when W runs further ahead) and the
-    // iterations in between
-    constexpr int PEND = (PW > PA ? BJ : 0) + (PA - 1) * NL;
-    static_assert(PMAX * NL <= 63, "outstanding loads within the vmcnt range");
-    // prologue: A[0 .. PA-1] and W[0 .. PW-1], interleaved by slice
-#pragma unroll
-    for (int s = 0; s < PMAX; ++s) {
-      unsigned kill;
-      const int koff = slice(s, kill);
-      if (s < PA) {
-#pragma unroll
-        for (int j = 0; j < AJ; ++j) issueA(j, koff, kill, s * ASTAGE);
-      }
-      if (s < PW) {
-#pragma unroll
-        for (int j = 0; j < BJ; ++j) issueW(j, koff, kill, s * WSTAGE);
-      }
-    }
     // One slice's loads are spread over its MFMAs: A[it + PA] first, then
     // W[it + PW].  State of the iteration: read and write stages, load operands.
     uint32_t raS = 0, rwS = 0, waS = PA * ASTAGE, wwS = PW * WSTAGE;
@@ -434,19 +452,25 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     wait_vm<0>();
     ring_barrier();
 
+    // this task's place, for its epilogue
+    const int em0 = m0, eMlim = Mlim, egrp0 = grp0;
+    const unsigned esp = sp, ent = nt;
+    task += per_xcd;
+    if (EARLY && task < hi) setup(task);
+
     // accumulator element r of a 32x32 tile: row 8*(r/4) + 4*(lane/32) + r%4, column lane%32
     if (splits > 1 || EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
       // float32 rows at the true output columns: split-K partials (the reduce
       // pass adds the splits in order and applies the epilogue), plain stores or
-      // residual adds.  The buffer ends at row Mlim, so rows past it are dropped.
+      // residual adds.  The buffer ends at row eMlim, so rows past it are dropped.
       const bool part = splits > 1;
       const int ld = part ? a.N : a.ldo;
-      float *base = part ? a.split_part + (size_t)sp * a.M_max * a.N : a.out_f32;
-      const int rw = m0 + wm * WM * 32;                 // the wave's first row
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(base + (size_t)rw * ld, (long long)max(Mlim - rw, 0) * ld * 4);
+      float *base = part ? a.split_part + (size_t)esp * a.M_max * a.N : a.out_f32;
+      const int rw = em0 + wm * WM * 32;                 // the wave's first row
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(base + (size_t)rw * ld, (long long)max(eMlim - rw, 0) * ld * 4);
 #pragma unroll
       for (int j = 0; j < WN; ++j) {
-        const int wr = group_wrow<EPI>(a, grp0 + wn * WN + j);
+        const int wr = group_wrow<EPI>(a, egrp0 + wn * WN + j);
         if (wr < 0) continue;
         const unsigned v0 = wr + l32 < a.N ? (unsigned)(4 * kh * ld + wr + l32) * 4 : OOB;
 #pragma unroll
@@ -469,15 +493,15 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     }
 
     // ------------------------------------------------------------ epilogues
-    const int rbase = m0 + wm * WM * 32 + 4 * (lane >> 5);
+    const int rbase = em0 + wm * WM * 32 + 4 * (lane >> 5);
     if (EPI == EPI_STORE_BF16 || EPI == EPI_SWIGLU) {
-      const int rw = m0 + wm * WM * 32;
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.out_bf16 + (size_t)rw * a.ldo, (long long)max(Mlim - rw, 0) * a.ldo * 2);
+      const int rw = em0 + wm * WM * 32;
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.out_bf16 + (size_t)rw * a.ldo, (long long)max(eMlim - rw, 0) * a.ldo * 2);
       constexpr int PAIR = EPI == EPI_SWIGLU ? 2 : 1;
       const int ncol = EPI == EPI_SWIGLU ? a.swiglu_inter : a.N;
 #pragma unroll
       for (int p = 0; p < WN / PAIR; ++p) {
-        const int col = (grp0 + wn * WN + PAIR * p) / PAIR * 32 + l32;
+        const int col = (egrp0 + wn * WN + PAIR * p) / PAIR * 32 + l32;
         const unsigned v0 = col < ncol ? (unsigned)(4 * kh * a.ldo + col) * 2 : OOB;
 #pragma unroll
         for (int i = 0; i < WM; ++i)
@@ -494,7 +518,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
       for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int p = 0; p < WN / 2; ++p) {
-          int grp = grp0 + wn * WN + 2 * p;
+          int grp = egrp0 + wn * WN + 2 * p;
           int head = grp / gph;
           if (head >= a.n_q + 2 * a.n_kv) continue;
           int wr = group_wrow<EPI>(a, grp);
@@ -502,27 +526,29 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             int gm = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
-            if (gm < Mlim) qkv_emit(a, gm, head, j, acc[i][2 * p][r], acc[i][2 * p + 1][r]);
+            if (gm < eMlim) qkv_emit(a, gm, head, j, acc[i][2 * p][r], acc[i][2 * p + 1][r]);
           }
         }
     } else if constexpr (EPI == EPI_ARGMAX || EPI == EPI_SAMPLE) {
       // One key per row and wave column range (WN * 32 columns), stored and
       // merged by a later pass.  Each lane first takes the maximum over its WN
-      // columns; the 32 column keys of each of 32 rows then go through LDS (idle
-      // after the k loop) and one lane per row takes their maximum, which avoids
+      // columns; the 32 column keys of each of 16 rows then go through LDS (the last
+      // W stage) and four lanes per row take their maximum, which avoids
       // a chain of dependent cross-lane shuffles per row.
-      constexpr int KS = 33;                        // keys per LDS row, one pad
-      static_assert((size_t)NWV * 32 * KS * 8 <= T::LDS, "key transpose fits the rings");
-      unsigned long long *kl = (unsigned long long *)lds + (size_t)wave * 32 * KS;
-      const int slot = nt * GN + wn;
-      const int col0 = (grp0 + wn * WN) * 32 + l32;   // this lane's column in group j: col0 + 32 j
+      static_assert((size_t)NWV * 16 * 32 * 8 <= WSTAGE, "key transpose fits one W stage");
+      unsigned long long *kl = (unsigned long long *)(lds + (NA * ASTAGE + PW * WSTAGE) / 2) + (size_t)wave * 16 * 32;
+      // key of (row, column lane), rows XORed apart over the banks
+      auto at = [](int row, int c) { return row * 32 + (c ^ row); };
+      const int mrow = lane & 15, mq = lane >> 4;    // this lane's row and quarter in the merges
+      const int slot = ent * GN + wn;
+      const int col0 = (egrp0 + wn * WN) * 32 + l32;   // this lane's column in group j: col0 + 32 j
       if (a.logits) {
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int gm = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
-            if (gm < Mlim)
+            if (gm < eMlim)
 #pragma unroll
               for (int j = 0; j < WN; ++j)
                 if (col0 + 32 * j < a.N) a.logits[(size_t)gm * a.ld_logits + col0 + 32 * j] = acc[i][j][r];
@@ -536,7 +562,9 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
         // branch-free per-lane maximum over the WN columns (increasing with j):
         // a strictly larger order key replaces, so the lowest column wins ties
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int r = 8 * half; r < 8 * half + 8; ++r) {
           float noise[WN];
           if constexpr (EPI == EPI_SAMPLE) {
             // one Philox call per row and lane covers this lane's WN columns:
@@ -563,23 +591,29 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
             bo = up ? o : bo;
             bc = up ? c : bc;
           }
-          const int q = 8 * (r >> 2) + 4 * kh + (r & 3);   // row within these 32
-          kl[q * KS + l32] = ((unsigned long long)bo << 32) | (0xffffffffu - bc);
+          const int q = 8 * ((r >> 2) & 1) + 4 * kh + (r & 3);   // row within these 16
+          kl[at(q, l32)] = ((unsigned long long)bo << 32) | (0xffffffffu - bc);
         }
         __builtin_amdgcn_wave_barrier();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (lane < 32) {
+        {
           unsigned long long best = 0ull;
-#pragma unroll 8
-          for (int c = 0; c < 32; ++c) {
-            const unsigned long long v = kl[lane * KS + c];
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const unsigned long long v = kl[at(mrow, 8 * mq + c)];
             best = v > best ? v : best;
           }
-          const int gm = m0 + wm * WM * 32 + i * 32 + lane;
-          if (gm < Mlim) a.amax_keys[(size_t)gm * a.amax_slots + slot] = best;
+#pragma unroll
+          for (int off = 16; off < 64; off <<= 1) {
+            const unsigned long long v = __shfl_xor(best, off, 64);
+            best = v > best ? v : best;
+          }
+          const int gm = em0 + wm * WM * 32 + i * 32 + 16 * half + mrow;
+          if (lane < 16 && gm < eMlim) a.amax_keys[(size_t)gm * a.amax_slots + slot] = best;
         }
         __builtin_amdgcn_wave_barrier();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
         if constexpr (EPI == EPI_SAMPLE) {
           // the row's log-partition partials over the same column range: each
           // lane's (max, rescaled sum) over its WN columns, merged per row
@@ -587,39 +621,45 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
           if (a.lse_part) {
             float2 *kf = (float2 *)kl;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              float x[WN];
-              float m = -__builtin_inff();
+            for (int half = 0; half < 2; ++half) {
 #pragma unroll
-              for (int j = 0; j < WN; ++j) {
-                x[j] = col0 + 32 * j < a.N ? acc[i][j][r] * a.inv_temp : -__builtin_inff();
-                m = fmaxf(m, x[j]);
+              for (int r = 8 * half; r < 8 * half + 8; ++r) {
+                float x[WN];
+                float m = -__builtin_inff();
+#pragma unroll
+                for (int j = 0; j < WN; ++j) {
+                  x[j] = col0 + 32 * j < a.N ? acc[i][j][r] * a.inv_temp : -__builtin_inff();
+                  m = fmaxf(m, x[j]);
+                }
+                float sum = 0.0f;
+#pragma unroll
+                for (int j = 0; j < WN; ++j) sum += __expf(x[j] - m);
+                if (m == -__builtin_inff()) sum = 0.0f;
+                kf[at(8 * ((r >> 2) & 1) + 4 * kh + (r & 3), l32)] = make_float2(m, sum);
               }
-              float sum = 0.0f;
-#pragma unroll
-              for (int j = 0; j < WN; ++j) sum += __expf(x[j] - m);
-              if (m == -__builtin_inff()) sum = 0.0f;
-              kf[(8 * (r >> 2) + 4 * kh + (r & 3)) * KS + l32] = make_float2(m, sum);
-            }
-            __builtin_amdgcn_wave_barrier();
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (lane < 32) {
+              __builtin_amdgcn_wave_barrier();
+              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+              float2 v[8];
               float m = -__builtin_inff();
-#pragma unroll 8
-              for (int c = 0; c < 32; ++c) m = fmaxf(m, kf[lane * KS + c].x);
+#pragma unroll
+              for (int c = 0; c < 8; ++c) {
+                v[c] = kf[at(mrow, 8 * mq + c)];
+                m = fmaxf(m, v[c].x);
+              }
+              m = fmaxf(m, __shfl_xor(m, 16, 64));
+              m = fmaxf(m, __shfl_xor(m, 32, 64));
               float sum = 0.0f;
               if (m != -__builtin_inff()) {
-#pragma unroll 8
-                for (int c = 0; c < 32; ++c) {
-                  const float2 v = kf[lane * KS + c];
-                  sum += v.y * __expf(v.x - m);
-                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) sum += v[c].y * __expf(v[c].x - m);
               }
-              const int gm = m0 + wm * WM * 32 + i * 32 + lane;
-              if (gm < Mlim) a.lse_part[(size_t)gm * a.amax_slots + slot] = make_float2(m, sum);
+              sum += __shfl_xor(sum, 16, 64);
+              sum += __shfl_xor(sum, 32, 64);
+              const int gm = em0 + wm * WM * 32 + i * 32 + 16 * half + mrow;
+              if (lane < 16 && gm < eMlim) a.lse_part[(size_t)gm * a.amax_slots + slot] = make_float2(m, sum);
+              __builtin_amdgcn_wave_barrier();
+              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
-            __builtin_amdgcn_wave_barrier();
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           }
         }
       };
@@ -628,8 +668,6 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
       if constexpr (WM > 1) row_block(std::integral_constant<int, 1>{});
       if constexpr (WM > 2) row_block(std::integral_constant<int, 2>{});
       if constexpr (WM > 3) row_block(std::integral_constant<int, 3>{});
-      // the next task's prologue refills the LDS this pass used
-      ring_barrier();
     }
   }
 }
