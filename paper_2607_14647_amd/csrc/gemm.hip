@@ -6,7 +6,7 @@
 //         160 KB of LDS, one workgroup per CU (dense GEMMs with many tiles);
 //   Small 128 x 128, four waves in a 2 x 2 grid, each wave 64 x 64;
 //         80 KB of LDS, two workgroups per CU (grouped MoE GEMMs, small shapes);
-//   Deep  128 x 128, eight waves, deeper rings, one workgroup per CU (float32 GEMMs, split-K).
+//   Deep  128 x 128, eight waves, deeper rings, one workgroup per CU (layer GEMMs at few rows).
 // Operands stream from memory straight into LDS (buffer loads with the LDS
 // destination, 128-byte rows of 64 k split in XOR-swizzled 16-byte chunks,
 // hardware zeros for rows and k beyond the operands).  A and W have rings of
@@ -85,6 +85,7 @@ using Big = Tile<4, 2, 2, 4, 2, 3, true>;
 using Mid = Tile<2, 4, 2, 2, 2, 3, true>;     // 128 x 256, eight waves in a 2 x 4 grid, 128 KB
 using Small = Tile<2, 2, 2, 2>;
 using Deep = Tile<2, 4, 2, 1, 3, 5>;          // 128 x 128, eight waves, three A and five W slices: 128 KB, one per CU
+using DeepPair = Tile<4, 2, 1, 2, 3, 5>;      // the same with two column groups per wave, for the paired epilogues
 using MidDeep = Tile<2, 4, 2, 2, 2, 4, true>;   // 128 x 256 with four W slices: the LM head at few live rows
 using BigFlat = Tile<4, 2, 2, 4>;   // Big without the skew: the sampling epilogue needs its registers
 
@@ -141,7 +142,7 @@ __device__ __forceinline__ int group_wrow(const GemmArgs &a, int grp) {
 }
 
 template <int EPI>
-__device__ __forceinline__ int n_col_tiles(const GemmArgs &a, int TN) {
+__host__ __device__ __forceinline__ int n_col_tiles(const GemmArgs &a, int TN) {
   return EPI == EPI_SWIGLU ? (a.swiglu_inter + TN / 2 - 1) / (TN / 2) : (a.N + TN - 1) / TN;
 }
 
@@ -678,30 +679,16 @@ k_gemm(GemmArgs a) {
   gemm_tasks<EPI, T, WPOL, GROUPED>(a);
 }
 
-// Dense GEMM whose tile shape follows the live row count M (read on the device):
-// SwiGLU: 128 x 256 tiles when they take fewer rounds of the persistent grid
-// than 256 x 256 tiles would (counting a 128-row task as half a 256-row one),
-// else 256 x 256.  Argmax LM head: 128 x 256 tiles with four W slices when the
-// last 256-row tile would be at most half full.  Every element is the
-// same sequence of MFMA k-steps in both shapes, so the choice never changes a
-// result bit.
+// Argmax LM head, its tile following the live row count M (read on the device):
+// 128 x 256 tiles with four W slices when the last 256-row tile would be at most half
+// full, else 256 x 256.  Every element is the same sequence of MFMA k-steps in both
+// shapes, so the choice never changes a result bit.
 template <int EPI, int WPOL>
 __global__ void __launch_bounds__(Big::THREADS)
 k_gemm_dual(GemmArgs a) {
-  static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for both tiles");
   static_assert(MidDeep::THREADS == Big::THREADS && MidDeep::LDS <= Big::LDS, "one launch shape for both tiles");
-  const int M = min(*a.m_count, a.M_max);
-  if constexpr (EPI == EPI_SWIGLU) {
-    // rounds of the persistent grid: a Mid task is half a Big one
-    const long long nct = n_col_tiles<EPI>(a, Big::TN), G = gridDim.x;
-    const long long big_rounds = ((M + Big::TM - 1) / Big::TM * nct + G - 1) / G;
-    const long long mid_rounds = ((M + Mid::TM - 1) / Mid::TM * nct + G - 1) / G;
-    if (mid_rounds < 2 * big_rounds) gemm_tasks<EPI, Mid, WPOL>(a);
-    else gemm_tasks<EPI, Big, WPOL>(a);
-  } else {
-    if (lm_head_mid_tile(M)) gemm_tasks<EPI, MidDeep, WPOL>(a);
-    else gemm_tasks<EPI, Big, WPOL>(a);
-  }
+  if (lm_head_mid_tile(min(*a.m_count, a.M_max))) gemm_tasks<EPI, MidDeep, WPOL>(a);
+  else gemm_tasks<EPI, Big, WPOL>(a);
 }
 
 // out[m][n] (+)= sum over splits of part[s][m][n], in split order (rows m < K*).
@@ -788,7 +775,7 @@ int cu_count() {
   return c;
 }
 
-// float32 GEMMs (QKV before RoPE, O, down, router), split over k or not: the tile
+// Layer GEMMs (QKV, O, gate-up, down, router), split over k or not: the tile
 // whose rounds of the persistent grid take least, at 0.64, 0.9 and 1.15 us per 64-k
 // slice (measured) for 128 x 128, 128 x 256 and 256 x 256 tiles: 32, 48 and 64 KB out
 // of L2 at 50-57 GB/s per CU.  So the large tile takes over where the rounds of the
@@ -798,33 +785,38 @@ int cu_count() {
 // 16 rows QKV 17.2 -> 14.4 us and O 15.1 -> 13.5 against a two-slice lead; from 128
 // rows on both leads measured the same.  Every element is the same sequence of MFMA
 // k-steps in all of them.
+//
+// The SwiGLU GEMM takes the same choice (4096 x 28672 with room for 256 rows: 200 live
+// rows 87 -> 71 us; 16 rows with room for 16 44 -> 40.6).
 template <int EPI, int WPOL>
 __device__ __forceinline__ void gemm_by_rows(const GemmArgs &a) {
+  using Flat = std::conditional_t<EPI == EPI_SWIGLU, DeepPair, Deep>;
+  static_assert(Flat::THREADS == Big::THREADS && Flat::LDS <= Big::LDS, "one launch shape for all tiles");
+  static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for all tiles");
   const unsigned M = min(*a.m_count, a.M_max), G = gridDim.x, sp = a.splits > 1 ? a.splits : 1;
   auto cost = [&](unsigned tm, unsigned tn, unsigned w) {
-    return ((M + tm - 1) / tm * ((a.N + tn - 1) / tn) * sp + G - 1) / G * w;
+    return ((M + tm - 1) / tm * (unsigned)n_col_tiles<EPI>(a, tn) * sp + G - 1) / G * w;
   };
-  const unsigned deep = cost(Deep::TM, Deep::TN, 64), mid = cost(Mid::TM, Mid::TN, 90), big = cost(Big::TM, Big::TN, 115);
-  // without split-K the RoPE epilogue needs both halves of a pair in one wave (two column
-  // groups), which the 128 x 128 tile's waves do not have
-  const bool paired = EPI == EPI_QKV_ROPE && sp == 1;
-  if (!paired && deep <= mid && deep <= big) gemm_tasks<EPI, Deep, WPOL>(a);
+  const unsigned flat = cost(Flat::TM, Flat::TN, 64), mid = cost(Mid::TM, Mid::TN, 90), big = cost(Big::TM, Big::TN, 115);
+  if (flat <= mid && flat <= big) {
+    // without split-K the RoPE epilogue needs both halves of a pair in one wave
+    if (EPI == EPI_QKV_ROPE && sp == 1) gemm_tasks<EPI, DeepPair, WPOL>(a);
+    else gemm_tasks<EPI, Flat, WPOL>(a);
+  }
   else if (mid <= big) gemm_tasks<EPI, Mid, WPOL>(a);
   else gemm_tasks<EPI, Big, WPOL>(a);
 }
 
 template <int EPI, int WPOL>
 __global__ void __launch_bounds__(Big::THREADS)
-k_gemm_f32(GemmArgs a) {
-  static_assert(Deep::THREADS == Big::THREADS && Deep::LDS <= Big::LDS, "one launch shape for all tiles");
-  static_assert(Mid::THREADS == Big::THREADS && Mid::LDS <= Big::LDS, "one launch shape for all tiles");
+k_gemm_rows(GemmArgs a) {
   gemm_by_rows<EPI, WPOL>(a);
 }
 
 template <int EPI, class T, int WPOL, bool GROUPED = false>
 int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   const int nMT = GROUPED ? a.m_tiles : (a.M_max + T::TM - 1) / T::TM;
-  const int nNT = EPI == EPI_SWIGLU ? (a.swiglu_inter + T::TN / 2 - 1) / (T::TN / 2) : (a.N + T::TN - 1) / T::TN;
+  const int nNT = n_col_tiles<EPI>(a, T::TN);
   if (a.splits > 1) return DCUT_EINVAL;
   if ((EPI == EPI_ARGMAX || EPI == EPI_SAMPLE) && (!a.amax_keys || a.amax_slots < nNT * T::GN))
     return DCUT_EINVAL;
@@ -838,17 +830,17 @@ int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   return launch(kid, k_gemm<EPI, T, WPOL, GROUPED>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
 }
 
-// k_gemm_f32 and, with split-K, the pass that adds the partials (unless the
+// k_gemm_rows and, with split-K, the pass that adds the partials (unless the
 // caller does).  One workgroup per CU, fewer when the 128 x 128 tasks are fewer.
 template <int EPI, int WPOL>
-int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
+int launch_rows(int kid, const GemmArgs &a, hipStream_t s) {
   const int splits = a.splits > 1 ? a.splits : 1;
   if (splits > 1 && (!a.split_part || a.N % 4 || (EPI != EPI_QKV_ROPE && a.ldo % 4))) return DCUT_EINVAL;
-  const long long tasks = (long long)((a.M_max + Deep::TM - 1) / Deep::TM) * ((a.N + Deep::TN - 1) / Deep::TN) * splits;
+  const long long tasks = (long long)((a.M_max + Deep::TM - 1) / Deep::TM) * n_col_tiles<EPI>(a, Deep::TN) * splits;
   long long g = cu_count();
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
-  DCUT_TRY(launch(kid, k_gemm_f32<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a));
+  DCUT_TRY(launch(kid, k_gemm_rows<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a));
   if (splits == 1 || a.defer_reduce) return DCUT_OK;
   if (EPI == EPI_QKV_ROPE) {
     const int quads = (a.n_q + 2 * a.n_kv) * (a.head_dim / 8);
@@ -859,26 +851,25 @@ int launch_f32(int kid, const GemmArgs &a, hipStream_t s) {
                 EPI == EPI_RESID_F32 ? 1 : 0);
 }
 
-// Grouped (MoE) GEMMs run on row tiles of 128 (Small); the float32 GEMMs choose
-// their tile on the device (k_gemm_f32).  The others: Big tiles with at least one
-// Big tile per CU at M_max rows (the SwiGLU and LM-head GEMMs pick Big or a
-// 128-row tile on the device from the live rows), Small tiles below that.
+// Grouped (MoE) GEMMs run on row tiles of 128 (Small); the layer GEMMs choose
+// their tile on the device (k_gemm_rows).  The LM heads: Big tiles with at least one
+// Big tile per CU at M_max rows (the argmax one picks Big or a 128-row tile on the
+// device from the live rows), Small tiles below that.
 template <int EPI, int WPOL>
 int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
   if (a.tiles) {
     if constexpr (EPI == EPI_SWIGLU || EPI == EPI_STORE_F32) return launch_tile<EPI, Small, WPOL, true>(kid, a, s);
     else return DCUT_EINVAL;
   }
-  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE) {
-    return launch_f32<EPI, WPOL>(kid, a, s);
+  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE || EPI == EPI_SWIGLU) {
+    return launch_rows<EPI, WPOL>(kid, a, s);
   } else {
-    const long long big_tasks = (long long)((a.M_max + Big::TM - 1) / Big::TM) *
-        (EPI == EPI_SWIGLU ? (a.swiglu_inter + Big::TN / 2 - 1) / (Big::TN / 2) : (a.N + Big::TN - 1) / Big::TN);
+    const long long big_tasks = (long long)((a.M_max + Big::TM - 1) / Big::TM) * ((a.N + Big::TN - 1) / Big::TN);
     if (big_tasks < cu_count()) return launch_tile<EPI, Small, WPOL>(kid, a, s);
-    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX) {
+    if constexpr (EPI == EPI_ARGMAX) {
       // tile shape chosen on the device from the live row count (one workgroup per CU);
       // the sampling epilogue keeps the 256-row tile (both paths in one kernel would spill)
-      if (EPI == EPI_ARGMAX && (!a.amax_keys || a.amax_slots < (a.N + MidDeep::TN - 1) / MidDeep::TN * MidDeep::GN))
+      if (!a.amax_keys || a.amax_slots < (a.N + MidDeep::TN - 1) / MidDeep::TN * MidDeep::GN)
         return DCUT_EINVAL;
       const int g = (cu_count() + 7) / 8 * 8;
       return launch(kid, k_gemm_dual<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
