@@ -8,13 +8,8 @@ namespace dcut {
 
 // Order-preserving map of a float to an unsigned key (larger float, larger key;
 // -inf maps above 0, so a key of 0 means "no candidate").
-__device__ __forceinline__ uint32_t orderable(float v) {
-  uint32_t u = __float_as_uint(v);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// The same key without a select: the sign smeared by an arithmetic shift,
-// with the top bit set, flips the magnitude bits of negative values only.
+// The sign smeared by an arithmetic shift, with the top bit set, flips the magnitude
+// bits of negative values only.
 __device__ __forceinline__ uint32_t order_key(float v) {
   const uint32_t u = __float_as_uint(v);
   return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);

@@ -9,7 +9,9 @@
 // ranking is the number of positions ahead of it, counted directly against every
 // other one: scores are read four at a time as LDS broadcasts and compared in 32
 // bits, which needs no sort network and no barrier, and splits over any number of
-// workgroups.  Up to 256 positions one 1024-thread workgroup does everything.
+// workgroups.  Up to 384 positions one 1024-thread workgroup does everything: calls
+// in a row with nothing else to do cost the host 12.4 us at 320 positions in one
+// launch and 15 in two; at 512 it is 16.6 and 15 (10.5 on the GPU).
 // Above, the N^2 comparisons of one workgroup would take longer than a launch, so
 // a first kernel ranks 16 positions per workgroup over the whole chip and the second,
 // one workgroup, does the rest (prefix sums, budget choice, keep depths, packing).
@@ -70,7 +72,7 @@ __device__ __forceinline__ double objective(unsigned long long P, double cost) {
   return ((double)P * 0x1p-40) / cost;
 }
 
-constexpr int SEL_FUSED_MAX = 256;     // positions ranked by the one-workgroup kernel
+constexpr int SEL_FUSED_MAX = 384;     // positions ranked by the one-workgroup kernel
 constexpr int RANK_THREADS = 512;
 
 __host__ __device__ constexpr int pad64(int n) { return (n + 63) & ~63; }
@@ -198,10 +200,10 @@ k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restri
     int *sc = (int *)(((uintptr_t)(s_cu + B + 1) + 15) & ~(uintptr_t)15);
     const bool bad = fill_scores(B, p.D, p.shift, conf, (float *)(sc + pad64(N)), sc);
     if (bad && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
-    static_assert(SEL_FUSED_MAX <= 16 * 16, "one wave per 16 positions");
-    const int NU = pad64(N) / 16, seg = lane >> 4, m = 16 * wv + (lane & 15);
-    if (wv < NU) {
-      int cnt = count_ahead(sc, wv, m, NU * seg / 4, NU * (seg + 1) / 4);
+    const int NU = pad64(N) / 16, seg = lane >> 4;
+    for (int u = wv; u < NU; u += 16) {
+      const int m = 16 * u + (lane & 15);
+      int cnt = count_ahead(sc, u, m, NU * seg / 4, NU * (seg + 1) / 4);
       cnt += __shfl_xor(cnt, 16, 64);
       cnt += __shfl_xor(cnt, 32, 64);
       if (lane < 16 && m < N) {

@@ -1,4 +1,4 @@
-"""Selection where its kernels change over: up to 256 positions in one launch, more in two."""
+"""Selection where its kernels change over: up to 384 positions in one launch, more in two."""
 import numpy as np
 import pytest
 
@@ -8,7 +8,7 @@ from tests.test_gpu_select import _costs, check
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,D", [(51, 4), (16, 15), (257, 0), (86, 2), (17, 15), (33, 30), (455, 17), (8192 // 64, 63)])
+@pytest.mark.parametrize("B,D", [(51, 4), (16, 15), (257, 0), (86, 2), (17, 15), (33, 30), (24, 15), (55, 6), (455, 17), (8192 // 64, 63)])
 @pytest.mark.parametrize("kind", ["mixed", "ties"])
 def test_select_rank_edges(B, D, kind):
     need_gpu()
