@@ -25,10 +25,10 @@
 // the kernel takes 145 (batch 64, 0.8 GB), with or without the tile barrier and with
 // a deeper ring, so the inner loop is kept short enough to hide: fragment addresses
 // are one per-lane constant with the k-step or column tile flipped in, tiles whose
-// keys every row sees take no masks, the softmax scale is folded into one fma per
-// score, and weights use the hardware exp2.  Batch 16 at 128 rows 33 -> 28 us, batch
-// 64 at 1024 rows 173 -> 165; groups of 8 heads (up to 128 rows, two row blocks per
-// wave in three workgroups per CU instead of 8 waves in two) 163 -> 152 us at batch 128.
+// keys every row sees take no masks, and weights use the hardware exp2.  Batch 16 at
+// 128 rows 33 -> 28 us, batch 64 at 1024 rows 173 -> 165; groups of 8 heads (up to 128
+// rows, two row blocks per wave in three workgroups per CU instead of 8 waves in two)
+// 163 -> 152 us at batch 128.
 //
 // Workgroup b takes item b of the longest-first work order (attn_plan.h),
 // which the layer's first norm kernel builds in one extra workgroup; batches
@@ -249,6 +249,7 @@ k_attn(AttnArgs a) {
     const bool full = p0 + KT <= min(kend, L + 1);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
+#pragma clang fp contract(off)     // the scaled scores' subtraction stays one (see below)
       if ((rb * NW + wave) * 16 >= R) break;   // uniform: no rows in this block or any later one
       // S^T: two blocks of 16 keys; lane owns keys 4 grp4 + j of each
       floatx4 s4[KT / 16];
@@ -270,11 +271,16 @@ k_attn(AttnArgs a) {
             if (p >= kend || p > kmax[rb]) s4[kb][j] = -__builtin_inff();
           }
       }
-      // tile maximum of the row in the exp2 domain (scores times sl2 > 0)
+      // Weights in the exp2 domain.  A score is scaled first and the maximum of the scaled
+      // scores subtracted, so the largest weight is exactly 1: scaled inside the
+      // subtraction's fma, a score past 2^31 keeps a rounding error of 2^7 and more, whose
+      // exp2 overflows.  Costs nothing (batch 64 at 1024 rows 638 us a layer both ways).
+#pragma unroll
+      for (int kb = 0; kb < KT / 16; ++kb) s4[kb] *= sl2;
       float tmax = fmaxf(fmaxf(s4[0][0], s4[0][1]), fmaxf(s4[0][2], s4[0][3]));
       tmax = fmaxf(tmax, fmaxf(fmaxf(s4[1][0], s4[1][1]), fmaxf(s4[1][2], s4[1][3])));
       tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64)) * sl2;
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
       const float m_new = fmaxf(m_run[rb], tmax);
       // a row that has seen no key yet keeps m = -inf; subtracting 0 then keeps its weights at 0
       const float sub = m_new == -__builtin_inff() ? 0.0f : m_new;
@@ -284,13 +290,13 @@ k_attn(AttnArgs a) {
       for (int kb = 0; kb < KT / 16; ++kb)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s4[kb][j], sl2, -sub));
+          const float pv = __builtin_amdgcn_exp2f(s4[kb][j] - sub);
           s4[kb][j] = pv;
           psum += pv;
         }
       psum += __shfl_xor(psum, 16, 64);
       psum += __shfl_xor(psum, 32, 64);
-      l_run[rb] = l_run[rb] * alpha + psum;
+      l_run[rb] = __builtin_fmaf(l_run[rb], alpha, psum);
       m_run[rb] = m_new;
 #pragma unroll
       for (int n = 0; n < NT; ++n) o[rb][n] *= alpha;
