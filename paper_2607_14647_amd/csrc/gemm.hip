@@ -175,6 +175,19 @@ __device__ __forceinline__ void qkv_emit(const GemmArgs &a, int gm, int head, in
   }
 }
 
+// First k of the slice after the one at k0, going round over the task's slices kt0 .. kt0 + nk - 1.
+constexpr __host__ __device__ int next_slice(int k0, int kt0, int nk) {
+  return k0 + TK == (kt0 + nk) * TK ? kt0 * TK : k0 + TK;
+}
+constexpr bool slices_in_range() {       // short and long loops, some turns past the last slice
+  for (int nk = 1; nk <= 6; ++nk)
+    for (int rot = 0; rot < nk; ++rot)
+      for (int it = 0, k0 = (3 + rot) * TK; it < 3 * nk + 6; ++it, k0 = next_slice(k0, 3, nk))
+        if (k0 != (3 + (rot + it) % nk) * TK) return false;
+  return true;
+}
+static_assert(slices_in_range(), "the slices in turn, none past the task's last");
+
 typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -205,7 +218,8 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   const int M = min(__builtin_amdgcn_readfirstlane(*a.m_count), a.M_max);
   const unsigned nMT = GROUPED ? __builtin_amdgcn_readfirstlane(*a.n_tiles) : (M + TM - 1) / TM;
   const unsigned nNT = n_col_tiles<EPI>(a, TN);
-  const int splits = a.splits > 1 ? a.splits : 1;
+  constexpr bool SPLIT = !GROUPED && (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE);
+  const int splits = SPLIT && a.splits > 1 ? a.splits : 1;
   const unsigned ntask = nMT * nNT * splits;
   const unsigned xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
   const unsigned lo = (unsigned)(((unsigned long long)ntask * xcd) >> 3);
@@ -232,6 +246,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   // One task's position and operand addresses; setup() fills them and starts the
   // task's first loads.
   int m0, Mlim, grp0, kt0, nk, rot;
+  int kA, kW;             // first k of the next A and W slices to load
   unsigned sp, nt;
   __amdgpu_buffer_rsrc_t rsA, rsW;
   unsigned aoff[AJ], boff[BJ];
@@ -239,12 +254,10 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   // stay fixed over the k loop.  `kill` is zero, or OOB for a slice past the
   // task's last (issued all the same, so that the count of loads in flight
   // stays constant) and for chunks beyond K in a slice that reaches past it.
-  auto slice = [&](int it, unsigned &kill) {
-    const int q = it + rot;
-    const int k0 = (kt0 + (q >= nk ? q - nk : q)) * TK;
-    kill = ((unsigned)(it >= nk) | (unsigned)(kchunk >= a.K - k0)) << 31;
-    return k0 * 2;
-  };
+  // The slices go round (next_slice), also past the last one, so that no scalar
+  // offset ever passes the operand's end.
+  auto kill = [&](int it, int k0) { return ((unsigned)(it >= nk) | (unsigned)(kchunk >= a.K - k0)) << 31; };
+  auto step = [&](int k0) { return next_slice(k0, kt0, nk); };
   auto issueA = [&](int j, int koff, unsigned kill, uint32_t stage) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void *)(uintptr_t)(lds0 + stage + (wave + NWV * j) * 1024), 16,
                                              aoff[j] | kill, koff, 0, 0);
@@ -321,19 +334,23 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
       boff[j] = wr < 0 ? OOB : (unsigned)((wr - wrow0 + RPI * (blk & 3) + lr) * a.ldw + kchunk) * 2;
     }
     // prologue: A[0 .. PA-1] and W[0 .. PW-1], interleaved by slice
+    int k0 = (kt0 + rot) * TK;
 #pragma unroll
     for (int q = 0; q < PMAX; ++q) {
-      unsigned kill;
-      const int koff = slice(q, kill);
+      const unsigned dead = kill(q, k0);
+      if (q == PA) kA = k0;
       if (q < PA) {
 #pragma unroll
-        for (int j = 0; j < AJ; ++j) issueA(j, koff, kill, q * ASTAGE);
+        for (int j = 0; j < AJ; ++j) issueA(j, k0 * 2, dead, q * ASTAGE);
       }
       if (q < PW) {
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) issueW(j, koff, kill, q * WSTAGE);
+        for (int j = 0; j < BJ; ++j) issueW(j, k0 * 2, dead, q * WSTAGE);
       }
+      k0 = step(k0);
     }
+    kW = k0;
+    if (PA == PMAX) kA = k0;
   };
 
   // The argmax LM head requests the next task's first slices before this one's
@@ -361,8 +378,12 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     int ka, kw;
     unsigned killA, killW;
     auto begin = [&](int it) {
-      ka = slice(it + PA, killA);
-      kw = slice(it + PW, killW);
+      ka = kA * 2;
+      kw = kW * 2;
+      killA = kill(it + PA, kA);
+      killW = kill(it + PW, kW);
+      kA = step(kA);
+      kW = step(kW);
     };
     auto advance = [&]() {
       raS = raS == (NA - 1) * ASTAGE ? 0 : raS + ASTAGE;

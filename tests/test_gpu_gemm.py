@@ -25,6 +25,9 @@ CASES = {
     "k_tail": _cfg(101, 12, 150, hidden=1000, inter=4104),
     # grouped expert GEMMs with the same remainders, every expert at a start of its own
     "k_tail_moe": _cfg(102, 12, 150, hidden=1000, inter=0, n_exp=9, top_k=2, exp_inter=200, rope_theta=1e6),
+    # one and two k slices (fewer than the rings hold) and a last row tile of one row
+    "k_short": _cfg(104, 129, 129, D=0, hidden=64, inter=72),
+    "k_short_moe": _cfg(105, 129, 129, D=0, hidden=64, inter=0, n_exp=5, top_k=2, exp_inter=8, rope_theta=1e6),
 }
 
 
