@@ -183,11 +183,13 @@ struct GemmArgs {
   int splits;
   float *split_part;
   int defer_reduce;               // with splits > 1: leave the partials for the caller to add
-  // grouped mode (MoE experts): row tiles come from a device list of
-  // (expert, first row, end row); W advances by w_stride elements per expert;
+  // grouped mode (MoE experts): row tiles come from a device list, each expert's
+  // together, of (expert + 256 * index of the expert's first tile, first row of the
+  // expert, end of its rows); W advances by w_stride elements per expert;
   // A rows are gathered through a_rows when it is not null.
   const int32_t *tiles;
   const int32_t *n_tiles;
+  int n_groups;             // experts
   int m_tiles;              // grid rows of tiles (upper bound of *n_tiles)
   long long w_stride;
   const int32_t *a_rows;

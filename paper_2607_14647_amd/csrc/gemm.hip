@@ -277,14 +277,29 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   static_assert(PMAX * NL <= 63, "outstanding loads within the vmcnt range");
 
   auto setup = [&](unsigned task) {
-    // grouped: column tile fastest, so an expert's rows are read by its column tiles at once
-    const unsigned rest = GROUPED ? task : task / nMT;
-    const unsigned mt = GROUPED ? task / nNT : task - rest * nMT;
-    sp = splits > 1 ? rest / nNT : 0;
-    nt = GROUPED ? task - mt * nNT : rest - sp * nNT;
-    m0 = mt * TM;
-    Mlim = M;
     const uint16_t *Wb = a.W;
+    int e = 0;
+    if constexpr (GROUPED) {
+      // experts slowest, an expert's row tiles fastest: the row tiles that multiply one
+      // slice of its weights run at the same time, and its rows are read by its column
+      // tiles in a row.  Task numbers of an expert start at its first tile's share.
+      // (uniform, but loaded through the vector path: kept scalar)
+      const int32_t *t = a.tiles + 3 * (task / nNT);
+      const int id = __builtin_amdgcn_readfirstlane(t[0]), first = __builtin_amdgcn_readfirstlane(t[1]);
+      Mlim = __builtin_amdgcn_readfirstlane(t[2]);
+      e = id & 255;
+      const unsigned q = task - (unsigned)(id >> 8) * nNT, nr = (Mlim - first + TM - 1) / TM;
+      nt = q / nr;
+      m0 = first + (q - nt * nr) * TM;
+      sp = 0;
+      Wb += (size_t)e * a.w_stride;
+    } else {
+      const unsigned rest = task / nMT;
+      sp = splits > 1 ? rest / nNT : 0;
+      nt = rest - sp * nNT;
+      m0 = (task - rest * nMT) * TM;
+      Mlim = M;
+    }
     kt0 = sp * per_split;
     nk = max(0, min(nk_all, kt0 + per_split) - kt0);
     grp0 = nt * (TN / 32);
@@ -294,11 +309,6 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     // Logits all start at k = 0: equal weight rows have to give equal logits.
     rot = 0;
     if constexpr (GROUPED) {
-      // uniform, but loaded through the vector path: kept scalar
-      const int e = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt]);
-      m0 = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt + 1]);
-      Mlim = __builtin_amdgcn_readfirstlane(a.tiles[3 * mt + 2]);
-      Wb += (size_t)e * a.w_stride;
       rot = nk > 0 ? (int)((e * nNT + nt) * 5u % (unsigned)nk) : 0;
     } else if (splits == 1 && EPI != EPI_ARGMAX && EPI != EPI_SAMPLE) {
       const unsigned n256 = (nNT * (TN / 32) + 7) / 8;
@@ -694,10 +704,10 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
   }
 }
 
-template <int EPI, class T, int WPOL, bool GROUPED>
+template <int EPI, class T, int WPOL>
 __global__ void __launch_bounds__(T::THREADS)
 k_gemm(GemmArgs a) {
-  gemm_tasks<EPI, T, WPOL, GROUPED>(a);
+  gemm_tasks<EPI, T, WPOL>(a);
 }
 
 // Argmax LM head, its tile following the live row count M (read on the device):
@@ -710,6 +720,22 @@ k_gemm_dual(GemmArgs a) {
   static_assert(MidDeep::THREADS == Big::THREADS && MidDeep::LDS <= Big::LDS, "one launch shape for both tiles");
   if (lm_head_mid_tile(min(*a.m_count, a.M_max))) gemm_tasks<EPI, MidDeep, WPOL>(a);
   else gemm_tasks<EPI, Big, WPOL>(a);
+}
+
+// Grouped (MoE expert) GEMM.  An expert's weights are read by its row tiles alone.  With
+// one row tile they are read once and streamed past the caches (non-temporal loads); with
+// more, the row tiles that run at the same time share each slice in L2, which the default
+// policy keeps.  The line lies where a third of the experts has a second row tile (E
+// experts, live tiles counted on the device).  Gate-up and down, us, streamed and default:
+// 128 experts of 2048 x 768, top-8: 768 rows 143 + 87 and 168 + 90, 1792 rows (112 an
+// expert) 183 + 109 and 200 + 109, 2048 rows 255 + 148 and 215 + 120; 8 experts of
+// 4096 x 14336, top-2: 400 rows 357 + 168 and 380 + 208, 480 rows 454 + 299 and 449 + 302,
+// 1024 rows 873 + 473 and 669 + 436.
+template <int EPI, class T>
+__global__ void __launch_bounds__(T::THREADS)
+k_gemm_grouped(GemmArgs a) {
+  if (3 * *a.n_tiles <= 4 * a.n_groups) gemm_tasks<EPI, T, CPOL_NT, true>(a);
+  else gemm_tasks<EPI, T, 0, true>(a);
 }
 
 // out[m][n] (+)= sum over splits of part[s][m][n], in split order (rows m < K*).
@@ -848,7 +874,8 @@ int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
   if (g < 8) g = 8;
-  return launch(kid, k_gemm<EPI, T, WPOL, GROUPED>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
+  if constexpr (GROUPED) return launch(kid, k_gemm_grouped<EPI, T>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
+  else return launch(kid, k_gemm<EPI, T, WPOL>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
 }
 
 // k_gemm_rows and, with split-K, the pass that adds the partials (unless the
@@ -872,16 +899,11 @@ int launch_rows(int kid, const GemmArgs &a, hipStream_t s) {
                 EPI == EPI_RESID_F32 ? 1 : 0);
 }
 
-// Grouped (MoE) GEMMs run on row tiles of 128 (Small); the layer GEMMs choose
-// their tile on the device (k_gemm_rows).  The LM heads: Big tiles with at least one
-// Big tile per CU at M_max rows (the argmax one picks Big or a 128-row tile on the
-// device from the live rows), Small tiles below that.
+// The layer GEMMs choose their tile on the device (k_gemm_rows).  The LM heads: Big
+// tiles with at least one Big tile per CU at M_max rows (the argmax one picks Big or a
+// 128-row tile on the device from the live rows), Small tiles below that.
 template <int EPI, int WPOL>
 int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
-  if (a.tiles) {
-    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_STORE_F32) return launch_tile<EPI, Small, WPOL, true>(kid, a, s);
-    else return DCUT_EINVAL;
-  }
   if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_STORE_F32 || EPI == EPI_QKV_ROPE || EPI == EPI_SWIGLU) {
     return launch_rows<EPI, WPOL>(kid, a, s);
   } else {
@@ -908,13 +930,16 @@ int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
 // with it.  Gate-up 4096 x 28672 at 16, 128 and 256 rows 45 -> 43, 56 -> 50 and
 // 71 -> 66 us, the whole batch-16 layer 179 -> 163; LM head 4096 x 128256 at 64 rows
 // 201 -> 187; at 1024 rows all the same.  Smaller ones (QKV 5120 x 2048 of a MoE
-// layer: 12.4 us by default, 13.9 streamed) may still be there.  Expert weights stream
-// at any size: a step's rows read most experts, 128 of them 1.2 GB (gate-up at 768
-// rows 176 -> 142 us, down 94 -> 88).
+// layer: 12.4 us by default, 13.9 streamed) may still be there.  Expert weights have a
+// rule of their own (k_gemm_grouped).
 template <int EPI>
 int launch_epi(int kid, const GemmArgs &a, hipStream_t s) {
   const long long w_rows = EPI == EPI_SWIGLU ? 2LL * a.swiglu_inter : a.N;
-  if (a.tiles || w_rows * a.ldw * 2 >= (64LL << 20)) return launch_policy<EPI, CPOL_NT>(kid, a, s);
+  if (a.tiles) {
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_STORE_F32) return launch_tile<EPI, Small, 0, true>(kid, a, s);
+    else return DCUT_EINVAL;
+  }
+  if (w_rows * a.ldw * 2 >= (64LL << 20)) return launch_policy<EPI, CPOL_NT>(kid, a, s);
   return launch_policy<EPI, 0>(kid, a, s);
 }
 

@@ -106,8 +106,8 @@ k_moe_route(const float *__restrict__ logits, int E, int k, int M_max, const int
 
 // One workgroup per expert: a stable counting sort of the K* * k assignments j =
 // row * k + slot by expert (each expert's assignments in increasing j, the order of
-// the keys (expert, j)), then the gather rows, inverse positions and the (expert,
-// first, end) row tiles.  Every workgroup counts all assignments by itself, so none
+// the keys (expert, j)), then the gather rows, inverse positions and the row tiles,
+// (expert and its first tile, its first row, its end) each.  Every workgroup counts all assignments by itself, so none
 // waits for another, and places its own expert's behind those of smaller experts; a
 // thread owns a run of consecutive assignments, so one scan orders them.  Bound by
 // latency: 6144 assignments of 128 experts 16.9 -> 7.4 us against one
@@ -147,8 +147,8 @@ k_moe_group(const int32_t *__restrict__ ids, int E, int k, int M_max, const int3
     }
   const int ntl = (own + TILE_M - 1) / TILE_M;
   for (int q = tid; q < ntl; q += 1024) {
-    tiles[3 * (tiles0 + q)] = me;
-    tiles[3 * (tiles0 + q) + 1] = rows + q * TILE_M;
+    tiles[3 * (tiles0 + q)] = me | tiles0 << 8;
+    tiles[3 * (tiles0 + q) + 1] = rows;
     tiles[3 * (tiles0 + q) + 2] = rows + own;
   }
   if (me == E - 1 && tid == 0) n_tiles[0] = tiles0 + ntl;
@@ -214,14 +214,14 @@ int moe_launch(const MoeArgs &m, hipStream_t s) {
   gu.A = m.h; gu.lda = m.H; gu.K = m.H; gu.M_max = A; gu.m_count = m.m_count;
   gu.W = m.w_gate_up; gu.ldw = m.H; gu.N = 2 * m.inter; gu.swiglu_inter = m.inter;
   gu.out_bf16 = mid; gu.ldo = m.inter;
-  gu.tiles = tiles; gu.n_tiles = ntiles; gu.m_tiles = L.max_tiles; gu.w_stride = (long long)2 * m.inter * m.H;
+  gu.tiles = tiles; gu.n_tiles = ntiles; gu.n_groups = m.E; gu.m_tiles = L.max_tiles; gu.w_stride = (long long)2 * m.inter * m.H;
   gu.a_rows = row_of; gu.a_extent = M;
   DCUT_TRY(gemm_launch(DCUT_KERNEL_GEMM_GATE_UP, EPI_SWIGLU, gu, s));
   GemmArgs dn = {};
   dn.A = mid; dn.lda = m.inter; dn.K = m.inter; dn.M_max = A; dn.m_count = m.m_count;
   dn.W = m.w_down; dn.ldw = m.inter; dn.N = m.H;
   dn.out_f32 = eo; dn.ldo = m.H;
-  dn.tiles = tiles; dn.n_tiles = ntiles; dn.m_tiles = L.max_tiles; dn.w_stride = (long long)m.H * m.inter;
+  dn.tiles = tiles; dn.n_tiles = ntiles; dn.n_groups = m.E; dn.m_tiles = L.max_tiles; dn.w_stride = (long long)m.H * m.inter;
   DCUT_TRY(gemm_launch(DCUT_KERNEL_GEMM_DOWN, EPI_STORE_F32, dn, s));
   return launch(DCUT_KERNEL_MOE, k_moe_combine, dim3(M), dim3(256), 0, s, (const float *)eo,
                 (const int32_t *)inv, (const float *)wts, m.H, m.top_k, m.m_count, m.x_out);

@@ -6,9 +6,10 @@ import dataclasses
 import numpy as np
 import pytest
 
+from oracle import layer as olay
 from paper_2607_14647_amd import workload as wl
-from tests.gpu_common import need_gpu, workload
-from tests.test_gpu_layer import _gpu_run, _layer_parity
+from tests.gpu_common import ROUTER_GAP, X_RTOL, need_gpu, note, row_rel_err, workload
+from tests.test_gpu_layer import _gpu_run, _layer_parity, _oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +55,33 @@ def test_tile_choice_keeps_bits():
         for i in range(_TILES.B):
             n = cu[i + 1] - cu[i]
             assert np.array_equal(x[cu[i]: cu[i + 1]], full[cf[i]: cf[i] + n]), i
+
+
+# experts of more than one 128-row tile: four of them with about 300 of 1200 assignments each, or
+# one of sixteen that every row takes (its first component is large in every row) and fifteen small ones
+_EXPERTS = {
+    "all_large": (_cfg(106, 40, 600, hidden=256, inter=0, n_exp=4, top_k=2, exp_inter=200, rope_theta=1e6), False),
+    "one_large": (_cfg(107, 20, 300, hidden=256, inter=0, n_exp=16, top_k=2, exp_inter=200, rope_theta=1e6), True),
+}
+
+
+@pytest.mark.parametrize("name", list(_EXPERTS))
+def test_experts_of_several_row_tiles(name):
+    need_gpu()
+    cfg, skew = _EXPERTS[name]
+    st, w, kv = workload(cfg, 0)
+    w = dict(w)
+    if skew:
+        w["embed"], w["w_router"] = w["embed"].copy(), w["w_router"].copy()
+        w["embed"][:, 0] = wl.bf16_round(np.float32([0.25]))[0]
+        w["w_router"][:, 0] = 0
+        w["w_router"][0, 0] = wl.bf16_round(np.float32([2.0]))[0]
+    K = cfg.budgets[0]
+    vs, _ = _gpu_run(cfg, st, w, kv, [K], [1.0])
+    _, lay, _, _ = _oracle(cfg, st, olay.prepare_weights(w), kv, K)
+    n = np.bincount(lay["router_ids"].ravel(), minlength=cfg.layer.n_exp)
+    ok = lay["router_gap"] > ROUTER_GAP
+    ex = row_rel_err(vs.x.cpu().numpy()[:K][ok], lay["x_out"][ok])
+    note(f"experts {name}: rows per expert {n.tolist()}, {ok.sum()}/{K} rows compared, max rel err {ex.max():.2e}")
+    assert n.max() > 256 and ok.sum() > K // 2
+    assert ex.max() <= X_RTOL
