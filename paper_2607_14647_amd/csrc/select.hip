@@ -9,21 +9,25 @@
 // ranking is the number of positions ahead of it, counted directly against every
 // other one: scores are read four at a time as LDS broadcasts and compared in 32
 // bits, which needs no sort network and no barrier, and splits over any number of
-// workgroups.  Up to 384 positions one 1024-thread workgroup does everything: calls
-// in a row with nothing else to do cost the host 12.4 us at 320 positions in one
-// launch and 15 in two; at 512 it is 16.6 and 15 (10.5 on the GPU).
-// Above, the N^2 comparisons of one workgroup would take longer than a launch, so
-// a first kernel ranks 16 positions per workgroup over the whole chip and the second,
-// one workgroup, does the rest (prefix sums, budget choice, keep depths, packing).
-// Against sorting 64-key runs and merging them in one workgroup: 4096 positions
-// (batch 256) 50.2 -> 15.6 us (both kernels), 1024 (batch 64)
-// 19.2 -> 10.9, 64 (batch 4) 8.7 -> 7.5.
+// workgroups.  Positions that score 1 by definition come first and are left out.
+// With up to 512 others one 1024-thread workgroup does everything, 32 positions a
+// wave.  Above, a first kernel ranks 16 positions per workgroup over the whole chip and
+// the second, one workgroup, does the rest (prefix sums, budget choice, keep depths,
+// packing).  The second launch costs the host 3 us, the comparisons of one workgroup
+// 4 us at 512 positions (and four times that at 1024): calls in a row with nothing else
+// to do, at 512 positions of 32 requests, take 12.1 us in one launch and 15.5 in two
+// (on the GPU 11.8 and 9.7), at 384 12.1 and 14.1 (10.0 and 9.6).
+// Against sorting 64-key runs and merging them in one workgroup, on the GPU: 64
+// positions (batch 4) 9.2 -> 7.3 us, 256 11.6 -> 8.6, 512 13.0 -> 11.8 (8 requests of 64:
+// 16.6 -> 15.7), 1024 (batch 64) 15.9 -> 10.2; 4096 (batch 256) 50.2 -> 15.6.
 //
 // Bit-exactness: each request's scores are one sequential float32 product per
 // depth (denormals kept, no contraction); the rank order (score descending, then
 // depth, then request) is total, so any correct count gives the same ranks;
 // benefits are integer sums of trunc(s * 2^40); the budget objective is one
 // float64 division.  The outputs are therefore identical on any hardware.
+#include <type_traits>
+
 #include "dcut_internal.h"
 #include "scan.h"
 
@@ -72,60 +76,86 @@ __device__ __forceinline__ double objective(unsigned long long P, double cost) {
   return ((double)P * 0x1p-40) / cost;
 }
 
-constexpr int SEL_FUSED_MAX = 384;     // positions ranked by the one-workgroup kernel
+constexpr int SEL_FUSED_MAX = 512;     // positions counted by the one-workgroup kernel: 32 a wave
 constexpr int RANK_THREADS = 512;
 
 __host__ __device__ constexpr int pad64(int n) { return (n + 63) & ~63; }
 
-// Scores of every position, as bits, into sc[k * B + i] (depth, then request: the
-// order of ties), one thread per request, sequential in depth; zeros up to a
-// multiple of 64.  s_conf: B * D floats of LDS.  Returns whether a confidence was bad.
-__device__ __forceinline__ bool fill_scores(int B, int D, int shift, const float *__restrict__ conf, float *s_conf,
-                                            int *sc) {
-  const int N = B * (D + 1);
+// Scores, as bits, of the positions k * B + i (depth, then request: the order of ties) of
+// the depths k from `skip` on, into sc[(k - skip) * B + i], one thread per request,
+// sequential in depth; zeros up to a multiple of 64.  s_conf: B * D floats of LDS.
+// Returns whether a confidence was bad.
+__device__ __forceinline__ bool fill_scores(int B, int D, int shift, int skip, const float *__restrict__ conf,
+                                            float *s_conf, int *sc) {
+  const int n = B * max(D + 1 - skip, 0);
   for (int j = threadIdx.x; j < B * D; j += blockDim.x) s_conf[j] = conf[j];
   __syncthreads();
   bool bad = false;
   for (int i = threadIdx.x; i < B; i += blockDim.x) {
     float s = 1.0f;
-    sc[i] = __float_as_int(s);
-    for (int k = 1; k <= D; ++k) {
-      float c = s_conf[i * D + (k - 1)];
-      if (conf_bad(c)) {
-        bad = true;
-        c = 0.0f;
+    if (skip == 0) sc[i] = __float_as_int(s);
+    const float *cf = s_conf + i * D;
+    int *at = sc + i - skip * B;
+    for (int k0 = 1; k0 <= D; k0 += 8) {
+      float c[8];                    // eight confidences at a time: their reads overlap
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c[u] = cf[min(k0 + u, D) - 1];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int k = k0 + u;
+        if (k > D) break;
+        const bool no = conf_bad(c[u]);
+        bad |= no;
+        const float prev = s;        // the shifted score of depth k: the product up to k - 1
+        s = s * (no ? 0.0f : c[u]);
+        if (k >= skip) at[k * B] = __float_as_int(shift ? prev : s);
       }
-      const float prev = s;          // the shifted score of depth k: the product up to k - 1
-      s = s * c;
-      sc[k * B + i] = __float_as_int(shift ? prev : s);
     }
   }
-  for (int j = N + threadIdx.x; j < pad64(N); j += blockDim.x) sc[j] = 0;
+  for (int j = n + threadIdx.x; j < pad64(n); j += blockDim.x) sc[j] = 0;
   __syncthreads();
   return bad;
 }
 
-// Positions of the 16-position units [lo, hi) ahead of position m (in unit mu) in
-// the ranking: a larger score, or an equal one earlier in the order of ties (bits
-// of scores are below 2^31, so "at least s" is "more than s - 1").  The zeros that
-// pad the last units come after every position and are ahead of none.
-__device__ __forceinline__ int count_ahead(const int *sc, int mu, int m, int lo, int hi) {
-  const int s = sc[m];
-  int cnt = 0;
+// This lane group's part of the counts of positions ahead of P positions, one in each of
+// the 16-position units mu .. mu + P - 1 (lane l16 of its unit): a larger score, or an
+// equal one earlier in the order of ties (bits of scores are below 2^31, so "at least s"
+// is "more than s - 1").  Group seg of those that share the positions takes the units
+// [lo, hi) and, if it is one of the first four, four places of their own units.  The zeros
+// that pad the last units come after every position and are ahead of none.
+template <int P>
+__device__ __forceinline__ void count_ahead(const int *sc, int mu, int l16, int seg, int lo, int hi, int (&cnt)[P]) {
+  int s[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    s[p] = sc[16 * (mu + p) + l16];
+    const int4 v = *(const int4 *)(sc + 16 * (mu + p) + 4 * (seg & 3));    // its own unit's equal scores before it
+    const int d = l16 - 4 * seg;
+    cnt[p] = (v.x == s[p] && d > 0) + (v.y == s[p] && d > 1) + (v.z == s[p] && d > 2) + (v.w == s[p] && d > 3);
+  }
   for (int u = lo; u < hi; ++u) {
     const int4 *q = (const int4 *)(sc + 16 * u);
-    if (u == mu) {
-      for (int j = 0; j < 16; ++j) cnt += sc[16 * u + j] > s - (16 * u + j < m ? 1 : 0);
-    } else {
-      const int thr = s - (u < mu ? 1 : 0);
+    int thr[P];
+    uint32_t ahead[P];               // the signs of thr - score, shifted in: two operations a score
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int4 v = q[j];
-        cnt += (v.x > thr) + (v.y > thr) + (v.z > thr) + (v.w > thr);
+    for (int p = 0; p < P; ++p) {
+      thr[p] = s[p] - (u < mu + p ? 1 : 0);
+      ahead[p] = 0;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int4 v = q[j];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        ahead[p] = __builtin_amdgcn_alignbit(ahead[p], (uint32_t)(thr[p] - v.x), 31);
+        ahead[p] = __builtin_amdgcn_alignbit(ahead[p], (uint32_t)(thr[p] - v.y), 31);
+        ahead[p] = __builtin_amdgcn_alignbit(ahead[p], (uint32_t)(thr[p] - v.z), 31);
+        ahead[p] = __builtin_amdgcn_alignbit(ahead[p], (uint32_t)(thr[p] - v.w), 31);
       }
     }
+#pragma unroll
+    for (int p = 0; p < P; ++p) cnt[p] += __popc(ahead[p]);
   }
-  return cnt;
 }
 
 // Ranks of 16 positions per workgroup (enough workgroups for the whole chip from
@@ -141,14 +171,15 @@ k_select_rank(int B, int D, int shift, const float *__restrict__ conf, int32_t *
   __shared__ int s_cnt[NW][16];
   const int N = B * (D + 1), NU = pad64(N) / 16;
   int *sc = s_rank_mem;                                      // [pad64(N)], then the confidences
-  const bool bad = fill_scores(B, D, shift, conf, (float *)(sc + pad64(N)), sc);
+  const bool bad = fill_scores(B, D, shift, 0, conf, (float *)(sc + pad64(N)), sc);
   if (bad && blockIdx.x == 0 && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
   const int l16 = threadIdx.x & 15, seg = threadIdx.x >> 4, wv = threadIdx.x >> 6;
   const int m = 16 * blockIdx.x + l16;
-  int cnt = count_ahead(sc, blockIdx.x, m, NU * seg / (4 * NW), NU * (seg + 1) / (4 * NW));
-  cnt += __shfl_xor(cnt, 16, 64);
-  cnt += __shfl_xor(cnt, 32, 64);
-  if ((threadIdx.x & 63) < 16) s_cnt[wv][l16] = cnt;
+  int c[1];
+  count_ahead(sc, blockIdx.x, l16, seg, NU * seg / (4 * NW), NU * (seg + 1) / (4 * NW), c);
+  c[0] += __shfl_xor(c[0], 16, 64);
+  c[0] += __shfl_xor(c[0], 32, 64);
+  if ((threadIdx.x & 63) < 16) s_cnt[wv][l16] = c[0];
   __syncthreads();
   if (threadIdx.x < 16 && m < N) {
     int r = 0;
@@ -196,21 +227,35 @@ k_select(SelectParams p, const float *__restrict__ conf, const int32_t *__restri
     zl[e] = idx < N ? ctx_len[idx / D1] : 0;
   }
   if constexpr (FUSED) {
-    // 1.-2. scores, and ranks: a wave per 16 positions, its lane groups sharing the list
-    int *sc = (int *)(((uintptr_t)(s_cu + B + 1) + 15) & ~(uintptr_t)15);
-    const bool bad = fill_scores(B, p.D, p.shift, conf, (float *)(sc + pad64(N)), sc);
+    // 1.-2. scores, and ranks.  The positions of depth 0 (and 1, shifted) score 1 and come
+    // first, in their order; of the others a wave takes 32, its lane groups sharing the list.
+    int *sc = (int *)s_mem + ((2 * pad64(N) + 2 * B + 1 + 3) & ~3);   // 16-byte aligned
+    const int first = B * min(D1, p.shift + 1);
+    const bool bad = fill_scores(B, p.D, p.shift, p.shift + 1, conf, (float *)(sc + pad64(N)), sc);
     if (bad && dev_err) atomicOr(dev_err, DCUT_DERR_CONF);
-    const int NU = pad64(N) / 16, seg = lane >> 4;
-    for (int u = wv; u < NU; u += 16) {
-      const int m = 16 * u + (lane & 15);
-      int cnt = count_ahead(sc, u, m, NU * seg / 4, NU * (seg + 1) / 4);
-      cnt += __shfl_xor(cnt, 16, 64);
-      cnt += __shfl_xor(cnt, 32, 64);
-      if (lane < 16 && m < N) {
-        s_rank[m] = cnt;
-        s_sort[cnt] = (uint32_t)sc[m];
-      }
+    if (tid < first) {
+      s_rank[tid] = tid;
+      s_sort[tid] = __float_as_uint(1.0f);
     }
+    const int NU = pad64(N - first) / 16, seg = lane >> 4, l16 = lane & 15;
+    auto rank_units = [&](auto pc) {
+      constexpr int P = decltype(pc)::value;
+      if (P * wv >= NU) return;
+      int cnt[P];
+      count_ahead(sc, P * wv, l16, seg, NU * seg / 4, NU * (seg + 1) / 4, cnt);
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        cnt[q] += __shfl_xor(cnt[q], 16, 64);
+        cnt[q] += __shfl_xor(cnt[q], 32, 64);
+        const int m = 16 * (P * wv + q) + l16, r = first + cnt[q];
+        if (lane < 16 && first + m < N) {
+          s_rank[first + m] = r;
+          s_sort[r] = (uint32_t)sc[m];
+        }
+      }
+    };
+    if (NU <= 16) rank_units(std::integral_constant<int, 1>{});
+    else rank_units(std::integral_constant<int, 2>{});
   } else {
 #pragma unroll
     for (int e = 0; e < EM; ++e) {
@@ -394,9 +439,10 @@ static int select_run(int B, int D, const float *conf, const int32_t *draft, con
     p.costs[r] = c;
   }
   const int N = B * (D + 1);
+  const int first = B * (D < shift ? 1 : shift + 1);     // positions of score 1 that come first anyway
   const size_t base = ((size_t)2 * pad64(N) + 2 * B + 1) * sizeof(uint32_t);   // ranks, sorted scores, keep depths, offsets
   const size_t scores = (size_t)pad64(N) * sizeof(uint32_t) + (size_t)B * D * sizeof(float);
-  if (N <= SEL_FUSED_MAX)
+  if (N <= 1024 && N - first <= SEL_FUSED_MAX)
     return launch(DCUT_KERNEL_SELECT, k_select<true>, dim3(1), dim3(1024), base + 16 + scores, stream, p, conf, draft,
                   ctx_len, keep_len, cu, packed_tok, packed_pos, packed_req, choice, (unsigned long long *)benefit,
                   dev_err, k_state);
