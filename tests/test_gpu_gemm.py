@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import layer as olay
+from oracle import select as osel
 from paper_2607_14647_amd import workload as wl
 from tests.gpu_common import ROUTER_GAP, X_RTOL, need_gpu, note, row_rel_err, workload
 from tests.test_gpu_layer import _gpu_run, _layer_parity, _oracle
@@ -38,8 +39,9 @@ def test_gemm_edges(name):
     _layer_parity(CASES[name], name, 0)
 
 
-# 1024 rows of a layer whose O and down projections split k: 128 x 128 tiles at 64 live rows,
-# 128 x 256 at 320, 256 x 256 at 1024 (chosen on the device from the live rows)
+# 1024 rows of a layer whose QKV and down projections split k (in four): 128 x 128 tiles at 64 live
+# rows; down takes 128 x 256 at 320 and 256 x 256 at 576 and 1024, QKV 128 x 256 at 1024 (chosen on
+# the device from the live rows)
 _TILES = _cfg(103, 64, 320, hidden=4096, n_q=8, n_kv=2, head_dim=128, inter=4096)
 
 
@@ -55,6 +57,44 @@ def test_tile_choice_keeps_bits():
         for i in range(_TILES.B):
             n = cu[i + 1] - cu[i]
             assert np.array_equal(x[cu[i]: cu[i + 1]], full[cf[i]: cf[i] + n]), i
+
+
+# 8192 rows of a layer that splits no k (31, 30 and 4 slices): QKV takes 128 x 128 tiles at 512 live
+# rows, 128 x 256 at 1024 and 256 x 256 from 1600 on; O and down 128 x 128 up to 1600, 128 x 256 at
+# 3000 and 256 x 256 at 8192
+_UNSPLIT = _cfg(108, 512, 3000, hidden=1984, n_q=15, n_kv=15, head_dim=128, inter=256)
+
+
+def test_unsplit_tile_choice_keeps_bits():
+    """The fused RoPE and cache append and the in-place residual add in every tile: residual rows and
+    appended keys and values of one run against those of all rows kept, bit for bit, and the first
+    requests of one run against the oracle."""
+    need_gpu()
+    cfg = dataclasses.replace(_UNSPLIT, ctx=("uniform", 0, 8))
+    st, w, kv = workload(cfg, 0)
+    ly, ctx = cfg.layer, st["ctx_len"]
+    full = _gpu_run(cfg, st, w, kv, [cfg.B * (cfg.D + 1)], [1.0])[0]
+    xf, cf = full.x.cpu().numpy(), full.host("cu")
+    kf, vf = (full.kv[n].cpu().numpy() for n in "kv")
+    for K in (512, 1024, 1600, 3000):
+        vs = _gpu_run(cfg, st, w, kv, [K], [1.0])[0]
+        x, cu = vs.x.cpu().numpy(), vs.host("cu")
+        rows = np.concatenate([cf[i] + np.arange(cu[i + 1] - cu[i]) for i in range(cfg.B)])
+        assert len(rows) == K and np.array_equal(x[:K], xf[rows]), K
+        for mine, theirs in ((vs.kv["k"].cpu().numpy(), kf), (vs.kv["v"].cpu().numpy(), vf)):
+            for i in range(cfg.B):
+                cap, n = int(kv["cap"][i]), int(cu[i + 1] - cu[i])
+                at = slice(kv["base"][i], kv["base"][i] + ly.n_kv * cap * ly.head_dim)
+                a, b = (t[at].reshape(ly.n_kv, cap, ly.head_dim)[:, : ctx[i] + n] for t in (mine, theirs))
+                assert np.array_equal(a, b), (K, i)
+        if K == 3000:
+            sel = osel.select(st["conf"], st["draft"], ctx, [K], [1.0])
+            assert np.array_equal(cu, sel["cu"])
+            lay = olay.verify_layer(ly, olay.prepare_weights(w), kv, sel["cu"], sel["packed_tok"], sel["packed_pos"],
+                                    sel["packed_req"], ctx, cfg.D, requests=range(32))
+            ex = row_rel_err(x[: cu[32]], lay["x_out"][: cu[32]])
+            note(f"unsplit tiles: {cu[32]} rows of {K} against the oracle, max rel err {ex.max():.2e}")
+            assert ex.max() <= X_RTOL
 
 
 # experts of more than one 128-row tile: four of them with about 300 of 1200 assignments each, or
