@@ -216,10 +216,13 @@ int gemm_splits(int M_max, int N, int K);
 // stride ldw (the span of one column tile: 256 rows, or the SwiGLU split point
 // plus 256 since a tile pairs gate and up rows).  Operands of any total size
 // pass as long as these spans stay below 2 GiB.
+constexpr long long GEMM_SPAN = 0x7fffffffLL - 256;
 inline bool gemm_span_ok(long long a_rows, long long lda, long long w_rows, long long ldw) {
-  const long long lim = 0x7fffffffLL - 256;
-  return a_rows * lda * 2 < lim && w_rows * ldw * 2 < lim;
+  return a_rows * lda * 2 < GEMM_SPAN && w_rows * ldw * 2 < GEMM_SPAN;
 }
+// Columns of the widest float32 output a layer may ask for: QKV, up to three times the
+// attention width, of which 256 bf16 rows lie within a span.
+constexpr long long MAX_QKV_COLS = 3 * (GEMM_SPAN / (256 * 2));
 
 // ---------------------------------------------------------------- other launchers
 // x[m] += sum of the split-K partials part[s][m] (in split order), then

@@ -494,12 +494,12 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
     if (splits > 1 || EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
       // float32 rows at the true output columns: split-K partials (the reduce
       // pass adds the splits in order and applies the epilogue), plain stores or
-      // residual adds.  The buffer ends at row eMlim, so rows past it are dropped.
+      // residual adds.  The buffer ends at row eMlim, so rows past it are dropped; each
+      // block of 32 rows has a buffer of its own, whose offsets stay below 2^31 at any width.
       const bool part = splits > 1;
       const int ld = part ? a.N : a.ldo;
+      static_assert(32 * 4 * MAX_QKV_COLS < 0x80000000LL, "a block's rows lie within 32-bit offsets");
       float *base = part ? a.split_part + (size_t)esp * a.M_max * a.N : a.out_f32;
-      const int rw = em0 + wm * WM * 32;                 // the wave's first row
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(base + (size_t)rw * ld, (long long)max(eMlim - rw, 0) * ld * 4);
 #pragma unroll
       for (int j = 0; j < WN; ++j) {
         const int wr = group_wrow<EPI>(a, egrp0 + wn * WN + j);
@@ -507,18 +507,20 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
         const unsigned v0 = wr + l32 < a.N ? (unsigned)(4 * kh * ld + wr + l32) * 4 : OOB;
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
+          const int rw = em0 + (wm * WM + i) * 32;         // the block's first row
+          const __amdgpu_buffer_rsrc_t rs = make_rsrc(base + (size_t)rw * ld, (long long)max(eMlim - rw, 0) * ld * 4);
           if (EPI == EPI_RESID_F32 && !part) {
             float old[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              old[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0));
+              old[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, v0 + (8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0));
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = old[r] + acc[i][j][r];
           }
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), rs,
-                                                  v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0);
+                                                  v0 + (8 * (r >> 2) + (r & 3)) * ld * 4, 0, 0);
         }
       }
       continue;
