@@ -141,7 +141,6 @@ inline bool batch_ok(int B, int D) {
 // C[M][N] = A[M][K] * W[N][K]^T in bf16 with float32 accumulation, for the rows
 // m < M_dev = *m_count (device), launched for M_max rows.
 enum EpiKind {
-  EPI_STORE_BF16 = 0,   // out_bf16[m][n]
   EPI_RESID_F32 = 1,    // out_f32[m][n] += acc   (residual add, in place)
   EPI_SWIGLU = 2,       // W rows interleaved by tile: out_bf16[m][j] = SiLU(gate) * up
   EPI_QKV_ROPE = 3,     // RoPE + scatter q to out_bf16, k/v into the cache
@@ -193,7 +192,7 @@ struct GemmArgs {
   int m_tiles;              // grid rows of tiles (upper bound of *n_tiles)
   long long w_stride;
   const int32_t *a_rows;
-  int a_extent;             // rows in the A buffer (0: M_max)
+  int a_extent;             // rows in the A buffer, given with a_rows
 };
 
 int gemm_launch(int kid, EpiKind epi, const GemmArgs &a, hipStream_t s);

@@ -528,21 +528,18 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 
     // ------------------------------------------------------------ epilogues
     const int rbase = em0 + wm * WM * 32 + 4 * (lane >> 5);
-    if (EPI == EPI_STORE_BF16 || EPI == EPI_SWIGLU) {
+    if constexpr (EPI == EPI_SWIGLU) {
       const int rw = em0 + wm * WM * 32;
       const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.out_bf16 + (size_t)rw * a.ldo, (long long)max(eMlim - rw, 0) * a.ldo * 2);
-      constexpr int PAIR = EPI == EPI_SWIGLU ? 2 : 1;
-      const int ncol = EPI == EPI_SWIGLU ? a.swiglu_inter : a.N;
 #pragma unroll
-      for (int p = 0; p < WN / PAIR; ++p) {
-        const int col = (egrp0 + wn * WN + PAIR * p) / PAIR * 32 + l32;
-        const unsigned v0 = col < ncol ? (unsigned)(4 * kh * a.ldo + col) * 2 : OOB;
+      for (int p = 0; p < WN / 2; ++p) {
+        const int col = (egrp0 + wn * WN + 2 * p) / 2 * 32 + l32;
+        const unsigned v0 = col < a.swiglu_inter ? (unsigned)(4 * kh * a.ldo + col) * 2 : OOB;
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            float v = acc[i][PAIR * p][r];
-            if constexpr (EPI == EPI_SWIGLU) v = silu(v) * acc[i][2 * p + 1][r];
+            const float v = silu(acc[i][2 * p][r]) * acc[i][2 * p + 1][r];
             __builtin_amdgcn_raw_buffer_store_b16(f2bf(v), rs, v0 + (i * 32 + 8 * (r >> 2) + (r & 3)) * a.ldo * 2, 0, 0);
           }
       }
@@ -918,10 +915,8 @@ int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
         return DCUT_EINVAL;
       const int g = (cu_count() + 7) / 8 * 8;
       return launch(kid, k_gemm_dual<EPI, WPOL>, dim3((unsigned)g), dim3(Big::THREADS), Big::LDS, s, a);
-    } else if constexpr (EPI == EPI_SAMPLE) {
-      return launch_tile<EPI, BigFlat, WPOL>(kid, a, s);
     } else {
-      return launch_tile<EPI, Big, WPOL>(kid, a, s);
+      return launch_tile<EPI, BigFlat, WPOL>(kid, a, s);
     }
   }
 }
@@ -995,7 +990,6 @@ void gemm_argmax_slots(const GemmArgs &a, EpiKind epi, int *big, int *mid) {
 
 int gemm_launch(int kid, EpiKind epi, const GemmArgs &a, hipStream_t s) {
   switch (epi) {
-    case EPI_STORE_BF16: return launch_epi<EPI_STORE_BF16>(kid, a, s);
     case EPI_RESID_F32: return launch_epi<EPI_RESID_F32>(kid, a, s);
     case EPI_SWIGLU: return launch_epi<EPI_SWIGLU>(kid, a, s);
     case EPI_QKV_ROPE: return launch_epi<EPI_QKV_ROPE>(kid, a, s);

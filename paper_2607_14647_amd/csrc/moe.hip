@@ -11,6 +11,7 @@
 // (expert, row * top_k + slot), so each expert's rows appear in row order,
 // and the combine adds the top_k expert outputs of a row in slot order.
 #include "dcut_internal.h"
+#include "rng.h"
 #include "scan.h"
 
 namespace dcut {
@@ -45,11 +46,6 @@ MoeWs moe_ws(int M, int H, int E, int k, int inter) {
   return w;
 }
 
-__device__ __forceinline__ uint32_t orderable(float v) {
-  uint32_t u = __float_as_uint(v);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 // One wave per row: top_k of the E router logits (largest first, ties to the
 // lower id) and their softmax weights renormalised over the chosen experts.
 __global__ void __launch_bounds__(256)
@@ -72,7 +68,7 @@ k_moe_route(const float *__restrict__ logits, int E, int k, int M_max, const int
     for (int j = 0; j < 4; ++j) {
       int e = lane + 64 * j;
       if (e < E && v[j] != -__builtin_inff()) {
-        unsigned long long key = ((unsigned long long)orderable(v[j]) << 32) | (0xffffffffu - (uint32_t)e);
+        unsigned long long key = ((unsigned long long)order_key(v[j]) << 32) | (0xffffffffu - (uint32_t)e);
         best = key > best ? key : best;
       }
     }
