@@ -105,7 +105,7 @@ k_attn(AttnArgs a) {
   constexpr int LPW = 2 * LPK;
   constexpr int NS = HD / 32;               // k-steps of the QK product
   constexpr int NT = HD / 16;               // 16-row tiles of O^T
-  __shared__ __align__(16) unsigned char ring[NSTAGE * STAGEB];
+  __shared__ __align__(ROWB) unsigned char ring[NSTAGE * STAGEB];   // fragment addresses flip bits within a row
 
   const int MC = a.max_chunks;
   const int tid = threadIdx.x, lane = tid & 63;
