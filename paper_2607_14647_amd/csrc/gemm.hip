@@ -1,19 +1,21 @@
 // bf16 NT GEMM on gfx950 MFMA with fused epilogues: C = A W^T, A [M][K], W [N][K].
 //
 // Tile shapes of one kernel template (32x32x16 bf16 MFMA, float32
-// accumulators, k-slices of 64):
-//   Big   256 x 256, eight waves in a 4 x 2 grid, each wave 64 x 128;
-//         160 KB of LDS, one workgroup per CU (dense GEMMs with many tiles);
-//   Small 128 x 128, four waves in a 2 x 2 grid, each wave 64 x 64;
-//         80 KB of LDS, two workgroups per CU (grouped MoE GEMMs, small shapes);
-//   Deep  128 x 128, eight waves, deeper rings, one workgroup per CU (layer GEMMs at few rows).
+// accumulators, k-slices of 64), with the A and W ring stages of each:
+//   Big      256 x 256, eight waves in a 4 x 2 grid, each wave 64 x 128, 2 + 3 stages:
+//            160 KB of LDS, one workgroup per CU (many live rows);
+//   Mid      128 x 256, eight waves, 2 + 3 stages; MidDeep 2 + 4 (LM head);
+//   Deep     128 x 128, eight waves, 3 + 5 stages, one workgroup per CU (few live
+//            rows); DeepPair the same for epilogues that pair column groups;
+//   Small    128 x 128, four waves in a 2 x 2 grid, each wave 64 x 64, 2 + 3 stages:
+//            80 KB of LDS, two workgroups per CU (grouped MoE GEMMs, small LM heads).
 // Operands stream from memory straight into LDS (buffer loads with the LDS
 // destination, 128-byte rows of 64 k split in XOR-swizzled 16-byte chunks,
 // hardware zeros for rows and k beyond the operands).  A and W have rings of
-// their own: A (activations, mostly L2-resident) two stages, W (weights,
-// streamed from HBM) three stages, so a W slice is requested two k-steps before
-// it is multiplied.  Fragment reads of the next 16-k step are issued before the
-// MFMAs of the current one.
+// their own: of A (activations, mostly L2-resident) one or two slices are in flight,
+// of W (weights, streamed from HBM) two to four, so a W slice is requested that many
+// k-steps before it is multiplied.  Fragment reads of the next 16-k step are issued
+// before the MFMAs of the current one.
 //
 // What bounds it and what the k loop does about it (measured with loads-only and
 // compute-only copies): a CU takes 45-60 GB/s out of L2 whatever the source, so at
@@ -36,7 +38,7 @@
 // workgroup reads the live row count M (K*) on the device and walks only the
 // tiles that exist, so rows beyond K* cost nothing.  Tasks (row tile, column
 // tile, k split) are numbered with the row tile fastest and the split slowest
-// and cut into eight contiguous ranges, one per XCD (the hardware deals
+// (grouped: expert by expert, an expert's row tiles fastest) and cut into eight contiguous ranges, one per XCD (the hardware deals
 // workgroups round-robin over the eight XCDs): row tiles sharing a W slice run
 // at the same time on the same L2, and an XCD reads the A columns of one or
 // two splits only, not all of A.
@@ -44,9 +46,10 @@
 // Determinism and causality: every output element is the same sequence of
 // MFMA k-steps whatever the tile shape (from the slice `rot` upwards, then from
 // k = 0; rot depends on the column's 256-column block, the expert and the
-// shapes only); split-K partials are added in split order; the tile shape and
-// split factor depend on M_max (the grid's row bound), never on M.  A row's bits therefore do not depend on which
-// or how many other rows are present.
+// shapes only); split-K partials are added in split order, and the split factor
+// depends on M_max (the grid's row bound), never on M.  The tile may follow M,
+// since it changes no bit.  A row's bits therefore do not depend on which or how
+// many other rows are present.
 //
 // Column groups: each 32-column MFMA tile loads a 32-row group of W chosen by
 // the epilogue, so that values an epilogue combines sit in the same lane:
@@ -922,13 +925,18 @@ int launch_policy(int kid, const GemmArgs &a, hipStream_t s) {
 }
 
 // Cache policy of the weight loads.  A matrix of 64 MB or more is streamed
-// (non-temporal): it is gone from the 256 MB memory-side cache before its next use,
-// and without the policy it takes the activations, partials and caches of the layer
-// with it.  Gate-up 4096 x 28672 at 16, 128 and 256 rows 45 -> 43, 56 -> 50 and
-// 71 -> 66 us, the whole batch-16 layer 179 -> 163; LM head 4096 x 128256 at 64 rows
-// 201 -> 187; at 1024 rows all the same.  Smaller ones (QKV 5120 x 2048 of a MoE
-// layer: 12.4 us by default, 13.9 streamed) may still be there.  Expert weights have a
-// rule of their own (k_gemm_grouped).
+// (non-temporal), so that it does not take the activations, partials and caches of the
+// layer out of the 256 MB memory-side cache.  Measured over ten layers with weights of
+// their own (no weight survives to its next use), us a layer, nothing streamed / this
+// rule / everything streamed: 4096 x 14336 layer at 16 rows 127.8 / 121.8 / 117.6, 128 rows
+// 166.6 / 158.3 / 159.7, 256 rows 211.3 / 208.6 / 207.3, 1024 rows 505.6 / 505.6 / 502.1,
+// 4096 rows 1866 / 1866 / 1863, 8192 rows 3885 / 3997 / 4009; 3072 x 8200 layer, whose down
+// matrix of 50 MB loses by it, at 128 rows 131.3 / 130.9 / 131.3, 512 rows 225.9 / 225.5 /
+// 234.5, 4096 rows 1147 / 1157 / 1191; attention matrices of the 2048-wide MoE layer
+// (20 MB) at 64 rows 287.5 / 287.6 / 284.5, 768 rows 392.1 / 391.6 / 395.9.  So below 64 MB
+// streaming gains 3 % at the fewest rows and loses up to 4 % above; from 64 MB on it gains
+// 5 % up to 128 rows and costs 3 % at 8192.  LM head 4096 x 128256 at 64 rows 201 -> 187.
+// Expert weights have a rule of their own (k_gemm_grouped).
 template <int EPI>
 int launch_epi(int kid, const GemmArgs &a, hipStream_t s) {
   const long long w_rows = EPI == EPI_SWIGLU ? 2LL * a.swiglu_inter : a.N;
