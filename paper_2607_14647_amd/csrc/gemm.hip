@@ -66,6 +66,12 @@ namespace dcut {
 
 namespace {
 
+// Two waves a SIMD is what the LDS of every tile allows, which the compiler cannot see
+// (dynamic LDS): told so, it keeps the k loop's order of loads, reads and MFMAs instead of
+// trading it for registers it does not need.  Sampling LM head 4096 x 16000 at 16 rows
+// 64.2 -> 58.0 us, 4096 x 8192 62.2 -> 56.2, batch-1 layer 115.7 -> 113.7; long ones alike.
+#define TWO_WAVES __attribute__((amdgpu_waves_per_eu(2, 2)))
+
 constexpr int TK = 64;       // k per LDS stage: one 128-byte row per operand row
 constexpr int CPR = TK / 8;  // 16-byte chunks per row
 constexpr int RPI = 64 / CPR;  // rows per 1 KB wave load
@@ -707,7 +713,7 @@ __device__ __forceinline__ void gemm_tasks(const GemmArgs &a) {
 }
 
 template <int EPI, class T, int WPOL>
-__global__ void __launch_bounds__(T::THREADS)
+__global__ void __launch_bounds__(T::THREADS) TWO_WAVES
 k_gemm(GemmArgs a) {
   gemm_tasks<EPI, T, WPOL>(a);
 }
@@ -717,7 +723,7 @@ k_gemm(GemmArgs a) {
 // full, else 256 x 256.  Every element is the same sequence of MFMA k-steps in both
 // shapes, so the choice never changes a result bit.
 template <int EPI, int WPOL>
-__global__ void __launch_bounds__(Big::THREADS)
+__global__ void __launch_bounds__(Big::THREADS) TWO_WAVES
 k_gemm_dual(GemmArgs a) {
   static_assert(MidDeep::THREADS == Big::THREADS && MidDeep::LDS <= Big::LDS, "one launch shape for both tiles");
   if (lm_head_mid_tile(min(*a.m_count, a.M_max))) gemm_tasks<EPI, MidDeep, WPOL>(a);
@@ -734,7 +740,7 @@ k_gemm_dual(GemmArgs a) {
 // 4096 x 14336, top-2: 400 rows 357 + 168 and 380 + 208, 480 rows 454 + 299 and 449 + 302,
 // 1024 rows 873 + 473 and 669 + 436.
 template <int EPI, class T>
-__global__ void __launch_bounds__(T::THREADS)
+__global__ void __launch_bounds__(T::THREADS) TWO_WAVES
 k_gemm_grouped(GemmArgs a) {
   if (3 * *a.n_tiles <= 4 * a.n_groups) gemm_tasks<EPI, T, CPOL_NT, true>(a);
   else gemm_tasks<EPI, T, 0, true>(a);
@@ -857,7 +863,7 @@ __device__ __forceinline__ void gemm_by_rows(const GemmArgs &a) {
 }
 
 template <int EPI, int WPOL>
-__global__ void __launch_bounds__(Big::THREADS)
+__global__ void __launch_bounds__(Big::THREADS) TWO_WAVES
 k_gemm_rows(GemmArgs a) {
   gemm_by_rows<EPI, WPOL>(a);
 }
