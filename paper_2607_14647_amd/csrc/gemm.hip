@@ -730,6 +730,19 @@ k_gemm_dual(GemmArgs a) {
   else gemm_tasks<EPI, Big, WPOL>(a);
 }
 
+// LM head in 128 x 128 tiles.  Weights worth streaming (`stream_tasks` not zero) are streamed
+// up to that many tasks, one per CU; with more, a second row tile reads the same slices
+// later and the default policy keeps them for it.  Ten weight matrices in turn, us, streamed and default: argmax 4096 x 16000 (125 column tiles)
+// 256 rows 54.1 and 56.0, 384 rows 84.3 and 74.1, 1024 rows 164.9 and 143.7; sampling
+// 4096 x 8192 (64) 512 rows 61.1 and 62.5, 768 rows 92.1 and 84.5.
+template <int EPI>
+__global__ void __launch_bounds__(Small::THREADS) TWO_WAVES
+k_gemm_head(GemmArgs a, unsigned stream_tasks) {
+  const unsigned M = min(*a.m_count, a.M_max);
+  if ((M + Small::TM - 1) / Small::TM * n_col_tiles<EPI>(a, Small::TN) <= stream_tasks) gemm_tasks<EPI, Small, CPOL_NT>(a);
+  else gemm_tasks<EPI, Small, 0>(a);
+}
+
 // Grouped (MoE expert) GEMM.  An expert's weights are read by its row tiles alone.  With
 // one row tile they are read once and streamed past the caches (non-temporal loads); with
 // more, the row tiles that run at the same time share each slice in L2, which the default
@@ -882,8 +895,11 @@ int launch_tile(int kid, const GemmArgs &a, hipStream_t s) {
   if (tasks < g) g = tasks;
   g = (g + 7) / 8 * 8;
   if (g < 8) g = 8;
-  if constexpr (GROUPED) return launch(kid, k_gemm_grouped<EPI, T>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
-  else return launch(kid, k_gemm<EPI, T, WPOL>, dim3((unsigned)g), dim3(T::THREADS), T::LDS, s, a);
+  const dim3 grid((unsigned)g), block(T::THREADS);
+  if constexpr (GROUPED) return launch(kid, k_gemm_grouped<EPI, T>, grid, block, T::LDS, s, a);
+  else if constexpr (std::is_same_v<T, Small>)
+    return launch(kid, k_gemm_head<EPI>, grid, block, T::LDS, s, a, WPOL == CPOL_NT ? (unsigned)cu_count() : 0u);
+  else return launch(kid, k_gemm<EPI, T, WPOL>, grid, block, T::LDS, s, a);
 }
 
 // k_gemm_rows and, with split-K, the pass that adds the partials (unless the
