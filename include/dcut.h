@@ -389,7 +389,11 @@ int dcut_nearest_batch(int B, int n, const int32_t *captured);
 /* Kernel timing hook for profilers.  Arms `kernel` (a DCUT_KERNEL_* id) on the
  * calling thread: its next launches on this thread record `start` before and
  * `stop` after the kernel on the launch stream (an id launched several times
- * per call keeps the last launch).  DCUT_KERNEL_NONE disarms.  This is the
+ * per call keeps the last launch; work of two launches, as the selection's of a
+ * large batch, has its start before the first and its stop after the last).  A call
+ * that has no use for the armed kernel does not launch it and records nothing (the
+ * attention merge where no request can have two key chunks, the residual and finish
+ * kernels without drafts).  DCUT_KERNEL_NONE disarms.  This is the
  * library's only state kept between calls: one (kernel, start, stop) triple per
  * host thread, which changes how the armed kernel is launched (with events)
  * but never what it computes.  The events must outlive the armed period.  In a routed-MoE
