@@ -68,8 +68,8 @@ namespace {
 
 // Two waves a SIMD is what the LDS of every tile allows, which the compiler cannot see
 // (dynamic LDS): told so, it keeps the k loop's order of loads, reads and MFMAs instead of
-// trading it for registers it does not need.  Sampling LM head 4096 x 16000 at 16 rows
-// 64.2 -> 58.0 us, 4096 x 8192 62.2 -> 56.2, batch-1 layer 115.7 -> 113.7; long ones alike.
+// trading it for registers it does not need.  Batch-1 layer 115.7 -> 113.7 us, smallest
+// step 72.1 -> 71.0, long kernels alike.
 #define TWO_WAVES __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 constexpr int TK = 64;       // k per LDS stage: one 128-byte row per operand row
@@ -742,11 +742,13 @@ k_gemm_dual(GemmArgs a) {
 
 // LM head in 128 x 128 tiles.  Weights worth streaming (`stream_tasks` not zero) are streamed
 // up to that many tasks, one per CU; with more, a second row tile reads the same slices
-// later and the default policy keeps them for it.  Ten weight matrices in turn, us, streamed and default: argmax 4096 x 16000 (125 column tiles)
-// 256 rows 54.1 and 56.0, 384 rows 84.3 and 74.1, 1024 rows 164.9 and 143.7; sampling
-// 4096 x 8192 (64) 512 rows 61.1 and 62.5, 768 rows 92.1 and 84.5.
-// (At least one wave a SIMD instead of two: the compiler then keeps the accumulators in
-// AGPRs; sampling 3072 x 12000 at 1024 rows 112.9 -> 107.4 us.)
+// later and the default policy keeps them for it.  Ten weight matrices in turn, us,
+// streamed and default: argmax 4096 x 16000 (125 column tiles) 256 rows 54.1 and 56.0, 384
+// rows 84.3 and 74.1, 1024 rows 164.9 and 143.7; sampling 4096 x 8192 (64) 512 rows 61.1
+// and 62.5, 768 rows 92.1 and 84.5.
+// Of the two waves a SIMD that LDS allows the compiler is asked for one only: it then
+// keeps the accumulators in AGPRs (sampling 3072 x 12000 at 1024 rows 112.9 -> 107.4 us)
+// and stays within 256 registers all the same.
 template <int EPI>
 __global__ void __launch_bounds__(Small::THREADS) __attribute__((amdgpu_waves_per_eu(1, 2)))
 k_gemm_head(GemmArgs a, unsigned stream_tasks) {
