@@ -5,11 +5,13 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import layer as olay
 from oracle import select as osel
+from paper_2607_14647_amd import lib as L
 from paper_2607_14647_amd import workload as wl
-from tests.gpu_common import ROUTER_GAP, X_RTOL, need_gpu, note, row_rel_err, workload
+from tests.gpu_common import LOGIT_RTOL, ROUTER_GAP, X_RTOL, need_gpu, note, row_rel_err, workload
 from tests.test_gpu_layer import _gpu_run, _layer_parity, _oracle
 
 pytestmark = pytest.mark.gpu
@@ -125,3 +127,41 @@ def test_experts_of_several_row_tiles(name):
     note(f"experts {name}: rows per expert {n.tolist()}, {ok.sum()}/{K} rows compared, max rel err {ex.max():.2e}")
     assert n.max() > 256 and ok.sum() > K // 2
     assert ex.max() <= X_RTOL
+
+
+@pytest.mark.parametrize("temperature", [0.0, 1.0])
+def test_small_vocabulary_head_keeps_bits(temperature):
+    """An LM head in 128 x 128 tiles (65 column tiles, 67 MB of weights) at 16 live rows, one task per CU
+    (two row tiles, weights streamed) and more (five, not streamed): the bits of a row depend on neither
+    the cache policy nor the row blocks that have no live row; logits against float64."""
+    need_gpu()
+    H, V, B, D = 4096, 8200, 40, 15
+    rows = B * (D + 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    w = (torch.randn(V, H, device="cuda", generator=g) * 0.02).bfloat16()
+    x = torch.randn(rows, H, device="cuda", generator=g)
+    gain = torch.ones(H, device="cuda", dtype=torch.bfloat16)
+    req = torch.arange(rows, device="cuda", dtype=torch.int32) % B
+    pos = torch.arange(rows, device="cuda", dtype=torch.int32) // B
+    ws = L.workspace(L.workspace_bytes(2, L.LayerCfg(hidden=H, vocab=V), B, D))
+    outs = {}
+    for K in (16, 256, 600):
+        cu = torch.full((B + 1,), K, device="cuda", dtype=torch.int32)
+        tok = torch.full((rows,), -1, device="cuda", dtype=torch.int32)
+        best, lse = (torch.full((rows,), -7.0, device="cuda") for _ in range(2))
+        logits = torch.full((rows, V), -7.0, device="cuda")
+        if temperature > 0.0:
+            L.lm_head_sample(H, V, B, D, cu, req, pos, x, gain, 1e-5, w, temperature, 11, tok, ws, max_score=best,
+                             logits=logits, lse=lse)
+        else:
+            L.lm_head_argmax(H, V, B, D, cu, x, gain, 1e-5, w, tok, ws, max_logit=best, logits=logits)
+        torch.cuda.synchronize()
+        outs[K] = (tok, best, lse, logits)
+        assert (tok[K:] == -1).all() and (logits[K:] == -7.0).all()
+    for K in (16, 256):
+        for a, b in zip(outs[K], outs[600]):
+            assert torch.equal(a[:K], b[:K]), K
+    h = x[:600].double() / torch.sqrt((x[:600].double() ** 2).mean(dim=1, keepdim=True) + 1e-5)
+    err = row_rel_err(outs[600][3][:600].cpu().numpy(), (h @ w.double().t()).cpu().numpy())
+    note(f"small vocabulary head T={temperature}: max rel err {err.max():.2e}")
+    assert err.max() <= LOGIT_RTOL
